@@ -17,7 +17,7 @@
 // MFMA products, as exact as fp32 products (128 x 128 tiles; 64 x 64 with the whole K
 // range staged at once for the latency-bound K <= 128 updates); on request they split
 // into two pieces and three products (about 2^-16 relative, faster) or run on MFMA
-// 32x32x2 f32 (exact fp32 products). fp64 tiles run on fp64 FMA. The adaptive ridge of Eq. 7, lambda_0 ||G||_F^2 / tr G, and
+// 32x32x2 f32 (exact fp32 products). fp64 tiles run on fp64 MFMA. The adaptive ridge of Eq. 7, lambda_0 ||G||_F^2 / tr G, and
 // the trace-mean scaling lambda_0 tr G / d are reduced on the device in fp64 in a fixed
 // order (deterministic).
 #include <math.h>
@@ -26,6 +26,7 @@
 #include <utility>
 
 #include "common.hpp"
+#include "gemm_f64.hpp"
 #include "kernels.hpp"
 
 namespace pkv {
@@ -678,55 +679,24 @@ __global__ __launch_bounds__(256, TERMS == 6 ? 1 : 2) void sgemm3s_kernel(SGemm 
   }
 }
 
-// ---- fp64: 64 x 64 output tile, fp64 FMA, 4 x 4 outputs per thread ----------------
-constexpr int D_T = 64, D_KC = 32;
-
-__device__ __forceinline__ void gemm_f64_body(const GemmDesc<double>& g, int t) {
-  __shared__ double As[D_KC][D_T + 1];
-  __shared__ double Bs[D_KC][D_T + 1];
+// ---- fp64: BM x BM output tile (64 or 32) on MFMA f64 ---------------------------------
+// A product of the d = 256 solve (K = 64 .. 256, latency bound): 5.9 us on 32-tiles, 25 on
+// 64-tiles of fp64 FMA with elementwise loads.
+template <int BM>
+__device__ __forceinline__ void gemm_f64_body(const GemmDesc<double>& g, int t, F64Lds<BM>& lds) {
   const int ti = t / g.tiles_n, tj = t % g.tiles_n;
+  const int i0 = ti * BM, j0 = tj * BM;
   if (g.lower && tj > ti) return;
-  const int i0 = ti * D_T, j0 = tj * D_T;
-  const int tid = threadIdx.x, ty = tid / 16, tx = tid % 16;
-  double acc[4][4] = {};
-  for (int k0 = 0; k0 < g.K; k0 += D_KC) {
-    for (int e = tid; e < D_T * D_KC; e += 256) {
-      int i, k;
-      if (g.sak == 1) { i = e / D_KC; k = e % D_KC; } else { k = e / D_T; i = e % D_T; }
-      const int gi = i0 + i, gk = k0 + k;
-      As[k][i] = (gi < g.M && gk < g.K) ? g.A[(int64_t)gi * g.sai + (int64_t)gk * g.sak] : 0.0;
-      int j, kb;
-      if (g.sbj == 1) { kb = e / D_T; j = e % D_T; } else { j = e / D_KC; kb = e % D_KC; }
-      const int gj = j0 + j, gkb = k0 + kb;
-      Bs[kb][j] = (gj < g.N && gkb < g.K) ? g.B[(int64_t)gkb * g.sbk + (int64_t)gj * g.sbj] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int kk = 0; kk < D_KC; ++kk) {
-      double a[4], b[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        a[u] = As[kk][ty * 4 + u];
-        b[u] = Bs[kk][tx * 4 + u];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fma(a[u], b[v], acc[u][v]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = i0 + ty * 4 + u, j = j0 + tx * 4 + v;
-      if (i < g.M && j < g.N) {
-        double* c = g.C + (int64_t)i * g.ldc + j;
-        const double r = g.alpha * acc[u][v];
-        *c = g.beta != 0.0 ? g.beta * *c + r : r;
-      }
-    }
+  f64x4 acc[BM / 32][BM / 32];
+  const F64Operand<double> A{g.A + i0 * g.sai, nullptr, g.sai, g.sak, g.M - i0};
+  const F64Operand<double> B{g.B + j0 * g.sbj, nullptr, g.sbj, g.sbk, g.N - j0};
+  f64_tile<BM>(acc, g.K, A, B, lds);
+  f64_each<BM>(acc, [&](int i, int j, double v) {
+    if (i0 + i >= g.M || j0 + j >= g.N) return;
+    double* c = g.C + (int64_t)(i0 + i) * g.ldc + j0 + j;
+    const double r = g.alpha * v;
+    *c = g.beta != 0.0 ? g.beta * *c + r : r;
+  });
 }
 
 // Up to two independent GEMM problems per launch: blocks [0, d0.ntiles) work on d0,
@@ -746,16 +716,18 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmDesc<float> d0, GemmD
   }
 }
 
+template <int BM>
 __global__ __launch_bounds__(256) void gemm_f64_kernel(GemmDesc<double> d0, GemmDesc<double> d1) {
+  __shared__ F64Lds<BM> lds;
   const int t = blockIdx.x;
   if (t < d0.ntiles) {
     int u = t;
     const GemmDesc<double> g = batch_item(d0, u);
-    gemm_f64_body(g, u);
+    gemm_f64_body<BM>(g, u, lds);
   } else if (t - d0.ntiles < d1.ntiles) {
     int u = t - d0.ntiles;
     const GemmDesc<double> g = batch_item(d1, u);
-    gemm_f64_body(g, u);
+    gemm_f64_body<BM>(g, u, lds);
   }
 }
 
@@ -1277,7 +1249,7 @@ void set_tiles(GemmDesc<T>& g, int tile) {
 }
 
 // One launch for up to two problems. fp32 uses 128 x 128 tiles unless that would
-// leave most of the 256 CUs idle, then 64 x 64.
+// leave most of the 256 CUs idle, then 64 x 64; fp64 64 x 64 and 32 x 32 by the same rule.
 template <class T>
 hipError_t run_group(const GemmDesc<T>* ds, int n, hipStream_t st) {
   GemmDesc<T> d[2] = {};
@@ -1296,9 +1268,15 @@ hipError_t run_group(const GemmDesc<T>* ds, int n, hipStream_t st) {
     else
       hipLaunchKernelGGL(gemm_f32_kernel<128>, dim3(total), dim3(256), 0, st, d[0], d[1]);
   } else {
-    for (int i = 0; i < m; ++i) set_tiles(d[i], D_T);
+    for (int i = 0; i < m; ++i) set_tiles(d[i], 64);
+    const bool small = d[0].ntiles + d[1].ntiles < 256;
+    if (small)
+      for (int i = 0; i < m; ++i) set_tiles(d[i], 32);
     const int total = d[0].ntiles + d[1].ntiles;
-    hipLaunchKernelGGL(gemm_f64_kernel, dim3(total), dim3(256), 0, st, d[0], d[1]);
+    if (small)
+      hipLaunchKernelGGL(gemm_f64_kernel<32>, dim3(total), dim3(256), 0, st, d[0], d[1]);
+    else
+      hipLaunchKernelGGL(gemm_f64_kernel<64>, dim3(total), dim3(256), 0, st, d[0], d[1]);
   }
   return hipGetLastError();
 }

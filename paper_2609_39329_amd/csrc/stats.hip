@@ -6,11 +6,12 @@
 // residual, and the student state through the patched block.
 //
 // fp32-accumulate path: split pre-passes + bgemm_kernel (bf16 MFMA, fp32 accumulation).
-// fp64-accumulate path (f64_gemm_kernel): plain fp64 FMA tiles through LDS.
+// fp64-accumulate path (f64_gemm_kernel): fp64 MFMA tiles through LDS.
 #include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
+#include "gemm_f64.hpp"
 #include "kernels.hpp"
 
 namespace pkv {
@@ -565,15 +566,6 @@ MlpWs mlp_layout(int64_t M, int64_t d, int64_t d_ff) {
 
 // ---------------------------------------------------------------- fp64 path
 
-template <class T>
-__device__ __forceinline__ double ld64(const T* p, int64_t i) {
-  return (double)p[i];
-}
-template <>
-__device__ __forceinline__ double ld64<__bf16>(const __bf16* p, int64_t i) {
-  return (double)(float)p[i];
-}
-
 template <class TA, class TB>
 struct F64Params {
   const TA* A1;
@@ -593,72 +585,58 @@ struct F64Params {
   int tiles_j;
 };
 
-// Out[i][j] (+)= sum_k A(i,k) B(j,k) (+ rho E), all products and sums in fp64.
-template <class TA, class TB>
-__global__ __launch_bounds__(256) void f64_gemm_kernel(F64Params<TA, TB> p) {
-  constexpr int T = 64, KC2 = 16;
-  __shared__ double As[KC2][T + 1];
-  __shared__ double Bs[KC2][T + 1];
-  const int i0 = (blockIdx.x / p.tiles_j) * T, j0 = (blockIdx.x % p.tiles_j) * T;
-  const int tid = threadIdx.x, ty = tid / 16, tx = tid % 16;
-  double acc[4][4] = {};
-  for (int k0 = 0; k0 < p.K; k0 += KC2) {
-    for (int e = tid; e < T * KC2; e += 256) {
-      int i, k;
-      if (p.sak == 1) { i = e / KC2; k = e % KC2; } else { k = e / T; i = e % T; }
-      double v = 0.0;
-      const int gi = i0 + i, gk = k0 + k;
-      if (gi < p.I && gk < p.K) {
-        const int64_t o = (int64_t)gi * p.sai + (int64_t)gk * p.sak;
-        v = ld64(p.A1, o) - (p.A2 ? ld64(p.A2, o) : 0.0);
-      }
-      As[k][i] = v;
-      int j, kb;
-      if (p.sbk == 1) { j = e / KC2; kb = e % KC2; } else { kb = e / T; j = e % T; }
-      double w = 0.0;
-      const int gj = j0 + j, gkb = k0 + kb;
-      if (gj < p.J && gkb < p.K) {
-        const int64_t o = (int64_t)gj * p.sbj + (int64_t)gkb * p.sbk;
-        w = ld64(p.B1, o) - (p.B2 ? ld64(p.B2, o) : 0.0);
-      }
-      Bs[kb][j] = w;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < KC2; ++k) {
-      double a[4], b[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        a[u] = As[k][ty * 4 + u];
-        b[u] = Bs[k][tx * 4 + u];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fma(a[u], b[v], acc[u][v]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = i0 + ty * 4 + u, j = j0 + tx * 4 + v;
-      if (i >= p.I || j >= p.J) continue;
-      double r = acc[u][v];
-      if (p.E1)
-        r += p.rho * ((double)p.E1[(int64_t)i * p.lde + j] - (double)p.E2[(int64_t)i * p.lde + j]);
-      double* o = p.Out + (int64_t)i * p.ldo + j;
-      *o = p.accumulate ? *o + r : r;
-    }
+// Out[i][j] (+)= sum_k A(i,k) B(j,k) (+ rho E), all products and sums in fp64 (MFMA f64).
+template <int BM, class TA, class TB>
+__device__ __forceinline__ void f64_gemm_body(const F64Params<TA, TB>& p, int t, F64Lds<BM>& lds) {
+  const int i0 = (t / p.tiles_j) * BM, j0 = (t % p.tiles_j) * BM;
+  f64x4 acc[BM / 32][BM / 32];
+  const F64Operand<TA> A{p.A1 + i0 * p.sai, p.A2 ? p.A2 + i0 * p.sai : nullptr, p.sai, p.sak, p.I - i0};
+  const F64Operand<TB> B{p.B1 + j0 * p.sbj, p.B2 ? p.B2 + j0 * p.sbj : nullptr, p.sbj, p.sbk, p.J - j0};
+  f64_tile<BM>(acc, p.K, A, B, lds);
+  f64_each<BM>(acc, [&](int ti, int tj, double r) {
+    const int i = i0 + ti, j = j0 + tj;
+    if (i >= p.I || j >= p.J) return;
+    if (p.E1)
+      r += p.rho * ((double)p.E1[(int64_t)i * p.lde + j] - (double)p.E2[(int64_t)i * p.lde + j]);
+    double* o = p.Out + (int64_t)i * p.ldo + j;
+    *o = p.accumulate ? *o + r : r;
+  });
 }
 
-template <class TA, class TB>
-hipError_t run_f64(F64Params<TA, TB> p, hipStream_t st) {
-  p.tiles_j = (p.J + 63) / 64;
-  const int ti = (p.I + 63) / 64;
-  hipLaunchKernelGGL((f64_gemm_kernel<TA, TB>), dim3(ti * p.tiles_j), dim3(256), 0, st, p);
+// One or two problems per launch: workgroups [0, n0) work on p, the rest on q.
+template <int BM, class TA, class TB, class TA1, class TB1>
+__global__ __launch_bounds__(256) void f64_gemm_kernel(F64Params<TA, TB> p, F64Params<TA1, TB1> q,
+                                                       int n0) {
+  __shared__ F64Lds<BM> lds;
+  const int t = blockIdx.x;
+  if (t < n0) f64_gemm_body<BM>(p, t, lds);
+  else f64_gemm_body<BM>(q, t - n0, lds);
+}
+
+// 64-tiles once they fill the 256 CUs, else 32-tiles (a call of few tiles is bound by the
+// latency of its K loop). d = 256, 128 rows: the targets 12 us (48 on 64-tiles of fp64 FMA),
+// G and C together 7 us (31 + 48).
+template <class TA, class TB, class TA1, class TB1>
+hipError_t run_f64(F64Params<TA, TB> p, F64Params<TA1, TB1> q, hipStream_t st) {
+  auto tiles = [](auto& x, int bm) {
+    x.tiles_j = (x.J + bm - 1) / bm;
+    return (x.I + bm - 1) / bm * x.tiles_j;
+  };
+  int n0 = tiles(p, 64), n1 = tiles(q, 64);
+  if (n0 + n1 >= 256) {
+    hipLaunchKernelGGL((f64_gemm_kernel<64, TA, TB, TA1, TB1>), dim3(n0 + n1), dim3(256), 0, st, p, q,
+                       n0);
+  } else {
+    n0 = tiles(p, 32);
+    n1 = tiles(q, 32);
+    hipLaunchKernelGGL((f64_gemm_kernel<32, TA, TB, TA1, TB1>), dim3(n0 + n1), dim3(256), 0, st, p, q,
+                       n0);
+  }
   return hipGetLastError();
+}
+template <class TA, class TB>
+hipError_t run_f64(const F64Params<TA, TB>& p, hipStream_t st) {
+  return run_f64(p, F64Params<TA, TB>{}, st);
 }
 
 }  // namespace
@@ -929,29 +907,26 @@ hipError_t launch_targets_f64(const float* Of, const float* Oc, const void* W, b
 hipError_t launch_normal_eq_f64(const float* X, const float* Yf, const float* Yc, const double* Yd,
                                 int64_t rows, int64_t din, int64_t dout, bool accumulate,
                                 double* G, double* C, hipStream_t st) {
-  {
-    F64Params<float, float> p{};
-    p.A1 = X; p.sai = 1; p.sak = din;
-    p.B1 = X; p.sbj = 1; p.sbk = din;
-    p.Out = G; p.ldo = din; p.accumulate = accumulate;
-    p.I = (int)din; p.J = (int)din; p.K = (int)rows;
-    hipError_t e = run_f64(p, st);
-    if (e != hipSuccess) return e;
-  }
+  // G and C in one launch
+  F64Params<float, float> g{};
+  g.A1 = X; g.sai = 1; g.sak = din;
+  g.B1 = X; g.sbj = 1; g.sbk = din;
+  g.Out = G; g.ldo = din; g.accumulate = accumulate;
+  g.I = (int)din; g.J = (int)din; g.K = (int)rows;
   if (Yd) {
     F64Params<float, double> p{};
     p.A1 = X; p.sai = 1; p.sak = din;
     p.B1 = Yd; p.sbj = 1; p.sbk = dout;
     p.Out = C; p.ldo = dout; p.accumulate = accumulate;
     p.I = (int)din; p.J = (int)dout; p.K = (int)rows;
-    return run_f64(p, st);
+    return run_f64(g, p, st);
   }
   F64Params<float, float> p{};
   p.A1 = X; p.sai = 1; p.sak = din;
   p.B1 = Yf; p.B2 = Yc; p.sbj = 1; p.sbk = dout;
   p.Out = C; p.ldo = dout; p.accumulate = accumulate;
   p.I = (int)din; p.J = (int)dout; p.K = (int)rows;
-  return run_f64(p, st);
+  return run_f64(g, p, st);
 }
 
 }  // namespace pkv
