@@ -86,14 +86,15 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
 // +1: a bf16 weight plus an fp32 patch). SRC float (hi and lo planes,
 // lo may be null for a bf16 source) or bf16 (hi plane only). Each thread reads 4
 // consecutive source columns (one vector load when vec is set: S1, S2 and ld allow
-// it), and 16 threads write one 256-byte run of a destination row.
+// it), and 16 threads write one 256-byte run of a destination row. pair >= 0: one of two
+// matrices interleaved in blocks of 32 destination rows, 64 apart, from row pair on.
 template <class SRC>
 __global__ __launch_bounds__(256) void split_transpose_kernel(const SRC* __restrict__ S1,
                                                               const float* __restrict__ S2, float s2,
                                                               int rows, int cols, int64_t ld,
                                                               __bf16* __restrict__ hi,
                                                               __bf16* __restrict__ lo, int rows_p,
-                                                              int cols_p, int vec) {
+                                                              int cols_p, int vec, int pair) {
   constexpr int TR = 128, TC = 64;
   __shared__ float tile[TR][TC + 1];
   const int r0 = blockIdx.y * TR, c0 = blockIdx.x * TC;
@@ -148,9 +149,38 @@ __global__ __launch_bounds__(256) void split_transpose_kernel(const SRC* __restr
       h[t] = to_bf16(v);
       l[t] = to_bf16(v - (float)h[t]);
     }
-    const int64_t o = (int64_t)c * rows_p + r0 + rr0;
+    const int row = pair < 0 ? c : (c / 32) * 64 + pair + c % 32;
+    const int64_t o = (int64_t)row * rows_p + r0 + rr0;
     *(bf16x8*)(hi + o) = h;
     if (lo) *(bf16x8*)(lo + o) = l;
+  }
+}
+
+// dst[c][r] = S[r][c] for a bf16 source of whole 16-byte row pieces (cols, ld multiples of 8,
+// aligned), zero outside; destination rows as split_transpose_kernel's. Memory bound: a lane
+// loads an 8 x 8 block (8 row pieces in flight), transposes it in registers and stores 8
+// pieces of destination rows; a wave's 8 x 8 lanes read and write whole 128-byte lines.
+// 4096 x 14336: 52 us (4.5 TB/s; 75 through a float tile in LDS).
+__global__ __launch_bounds__(256) void transpose_bf16_kernel(const __bf16* __restrict__ S, int rows,
+                                                             int cols, int64_t ld,
+                                                             __bf16* __restrict__ dst, int rows_p,
+                                                             int cols_p, int pair) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int r0 = blockIdx.y * 128 + (wid >> 1) * 64 + (lane >> 3) * 8;
+  const int c0 = blockIdx.x * 128 + (wid & 1) * 64 + (lane & 7) * 8;
+  if (r0 >= rows_p || c0 >= cols_p) return;
+  u32x4 in[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    in[i] = r0 + i < rows && c0 < cols ? *(const u32x4*)(S + (int64_t)(r0 + i) * ld + c0) : u32x4{};
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    u32x4 v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)  // rows 2 k, 2 k + 1 of column c
+      v[k] = __builtin_amdgcn_perm(in[2 * k + 1][c / 2], in[2 * k][c / 2], c % 2 ? 0x07060302u : 0x05040100u);
+    const int row = pair < 0 ? c0 + c : ((c0 + c) / 32) * 64 + pair + (c0 + c) % 32;
+    *(u32x4*)(dst + (int64_t)row * rows_p + r0) = v;
   }
 }
 
@@ -164,22 +194,27 @@ __global__ __launch_bounds__(256) void split_transpose_kernel(const SRC* __restr
 // accesses. SYM: only tiles with tile_i <= tile_j; the diagonal tiles keep their i <= j
 // half and every tile is mirrored, so the result is exactly symmetric.
 //
-// Two tile shapes (BgTile<T>):
-//   T = 256: 8 waves of 128 x 64, two LDS stages; one 256-tile per CU fills the chip
-//     for a 4096 x 4096 output (16 x 16 tiles).
-//   T = 192: 8 waves, two per 96 x 96 quadrant (nine accumulators each): wave w takes
-//     the first 16 k of every 32-k chunk, wave w + 4 (on the same SIMD) the second 16,
-//     and the two partial tiles are summed once at the end through LDS. Three LDS
-//     stages; waves 0-3 load the A planes, waves 4-7 the B planes. The symmetric
-//     products use it: a 4096-wide triangle is 253 tiles of 192 (one round on 256 CUs)
-//     against 136 of 256.
+// Tile shapes (BgCfg), eight waves each. The products are bound by LDS reads and the barrier
+// per chunk next to the MFMAs, so a wave's tile is wide on the side with fewer planes, and
+// the next 16 k are read from LDS while the current ones are multiplied (u [Wg | Wu] of the
+// MLP at M = 4096, 1.92 TFLOP of MFMA work: 1.57 -> 1.42 ms):
+//   256 x 256, waves of 128 x 64 (64 x 128 with two A planes and one B plane), two or three
+//     stages: one tile per CU fills the chip for a 4096 x 4096 output;
+//   128 x 256 and 128 x 128, waves of 64 x 64 and 64 x 32: outputs of fewer tiles;
+//   symmetric products, 192 x 192: two waves per 96 x 96 quadrant (nine accumulators
+//     each): wave w takes the first 16 k of every 32-k chunk, wave w + 4 (on the same
+//     SIMD) the second 16, and the two partial tiles are summed once at the end through
+//     LDS. Three LDS stages; waves 0-3 load the A planes, waves 4-7 the B planes. A
+//     4096-wide triangle is 253 tiles of 192 (one round on 256 CUs) against 136 of 256.
 // A tile's K chunk goes from HBM straight into LDS (buffer_load ... lds; no staging
 // registers) while earlier chunks are multiplied. Rows past a plane's end (the last
 // 192-tile reaches past a 256-padded plane) read as zeros through the buffer range.
 struct BGemm {
   const __bf16* A[2];  // planes of A [Ip][Kp]
-  const __bf16* B[2];  // planes of B [Jp][Kp]
+  const __bf16* B[2];  // planes of B [Jp][Kp]; BNAT: the bf16 matrix itself, [K][ldb] (SWIGLU: gate, up)
   int64_t ld;          // Kp
+  int64_t ldb;         // BNAT: row length of B
+  int K;               // BNAT: rows of B
   float* Out;
   int64_t ldo;
   const float* E1;
@@ -194,38 +229,36 @@ struct BGemm {
 
 constexpr int BG_KC = 32;    // contraction chunk per LDS stage
 constexpr int BG_GROUP = 4;  // tile rows per group of the non-symmetric tile order
-template <int T>
-struct BgTile;
-template <>
-struct BgTile<256> {
-  static constexpr int WM = 128, WN = 64, STAGES = 2, KSPLIT = 1;
+// TI x TJ output tile of waves of WM x WN, S LDS stages, KSP waves per wave tile (each a
+// part of the k range)
+template <int TI_, int TJ_, int WM_, int WN_, int S_, int KSP_>
+struct BgCfg {
+  static constexpr int TI = TI_, TJ = TJ_, WM = WM_, WN = WN_, S = S_, KSP = KSP_;
+  static constexpr int NTH = (TI / WM) * (TJ / WN) * KSP * 64;
 };
-template <>
-struct BgTile<192> {
-  static constexpr int WM = 96, WN = 96, STAGES = 3, KSPLIT = 2;
-};
-template <int T>
-constexpr int bg_threads() {
-  return (T / BgTile<T>::WM) * (T / BgTile<T>::WN) * BgTile<T>::KSPLIT * 64;
-}
+using BgSym = BgCfg<192, 192, 96, 96, 3, 2>;
 
-template <int T, int NA, int NB, int NT, int TA, int TB, bool SYM>
-__global__ __launch_bounds__(bg_threads<T>(), 1) void bgemm_kernel(BGemm p) {
-  constexpr int WM = BgTile<T>::WM, WN = BgTile<T>::WN, S = BgTile<T>::STAGES;
-  constexpr int KSP = BgTile<T>::KSPLIT;
-  constexpr int NTH = bg_threads<T>();
-  constexpr int ROWS = (NA + NB) * T;              // stacked plane rows per stage
+template <class CFG, int NA, int NB, int NT, int TA, int TB, bool SYM, bool BNAT, bool SWIGLU>
+__global__ __launch_bounds__(CFG::NTH, 1) void bgemm_kernel(BGemm p) {
+  static_assert(!BNAT || (NB == 1 && CFG::KSP == 1 && !SYM && CFG::NTH == 512), "one plane of B as stored");
+  static_assert(!SWIGLU || (!SYM && (CFG::WN / 32) % 2 == 0), "gate and up blocks side by side");
+  constexpr int TI = CFG::TI, TJ = CFG::TJ, WM = CFG::WM, WN = CFG::WN, S = CFG::S;
+  constexpr int KSP = CFG::KSP, NTH = CFG::NTH;
+  constexpr int ROWS = NA * TI + NB * TJ;          // stacked plane rows per stage
   // KSP = 1: all threads load every plane; KSP = 2: threads [0, NTH/2) the A planes,
   // [NTH/2, NTH) the B planes
   constexpr int LTH = KSP == 1 ? NTH : NTH / 2;    // threads loading one plane
   constexpr int RPU = LTH / 4;                     // rows per load round (4 chunks per row)
-  constexpr int PPR = T / RPU;                     // load rounds per plane
+  constexpr int PPA = TI / RPU, PPB = TJ / RPU;    // load rounds per A, B plane
   constexpr int LPT = ROWS * (BG_KC / 8) / NTH;    // 16-byte loads per thread per stage
   constexpr int MA = WM / 32, MB = WN / 32;
-  static_assert(KSP == 1 || (KSP == 2 && NA == NB), "split loads: as many A as B planes");
-  static_assert(T % RPU == 0 && LPT == PPR * (KSP == 1 ? NA + NB : NA), "whole load rounds per plane");
+  static_assert(KSP == 1 || (KSP == 2 && NA == NB && TI == TJ), "split loads: as many A as B rows");
+  static_assert(TI % RPU == 0 && TJ % RPU == 0, "whole load rounds per plane");
+  static_assert(LPT == (KSP == 1 ? NA * PPA + NB * PPB : NA * PPA), "whole load rounds per stage");
   static_assert(BG_KC == 32 && (KSP == 1 || KSP == 2), "one or two 16-k halves per chunk");
-  static_assert(WM % 16 == 0 && WN % 16 == 0 && T % 16 == 0, "fragment rows aligned to the swizzle");
+  static_assert(WM % 16 == 0 && WN % 16 == 0 && TI % 16 == 0 && TJ % 16 == 0,
+                "fragment rows aligned to the swizzle");
+  static_assert(S * ROWS * BG_KC * 2 <= 160 * 1024, "the stages fit in LDS");
   __shared__ __attribute__((aligned(16))) __bf16 lds[S][ROWS * BG_KC];
   int ti, tj;
   {
@@ -252,12 +285,12 @@ __global__ __launch_bounds__(bg_threads<T>(), 1) void bgemm_kernel(BGemm p) {
       tj = r / rows;
     }
   }
-  const int i0 = ti * T, j0 = tj * T;
+  const int i0 = ti * TI, j0 = tj * TJ;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int h32 = lane >> 5, l32 = lane & 31;
-  constexpr int NQW = (T / WM) * (T / WN);  // waves per k half
+  constexpr int NQW = (TI / WM) * (TJ / WN);  // waves per k half
   const int wq = wid % NQW, kh = wid / NQW;  // output block, k half (KSP = 2)
-  const int wi = (wq / (T / WN)) * WM, wj = (wq % (T / WN)) * WN;
+  const int wi = (wq / (TJ / WN)) * WM, wj = (wq % (TJ / WN)) * WN;
   const int nq = p.Kp / BG_KC;
 
   f32x16 acc[MA][MB];
@@ -269,17 +302,18 @@ __global__ __launch_bounds__(bg_threads<T>(), 1) void bgemm_kernel(BGemm p) {
   // Stages of unpadded [stacked row][32 k] tiles. LDS position c of a stage (16 bytes)
   // holds stacked row c / 4, k chunk (c % 4) ^ ((row / 4) % 4): the 16 consecutive rows
   // an MFMA fragment read takes at one k chunk land in 16 different bank groups. Load u
-  // (u < LPT) of thread tid fills row (u % PPR) * RPU + lt / 4 of plane u / PPR (KSP =
-  // 1; lt = tid) or of plane (tid < NTH/2 ? 0 : NA) + u / PPR (KSP = 2; lt = tid % (NTH/2)).
+  // (u < LPT) of thread tid fills stacked row u * RPU + tid / 4 (KSP = 1), or row
+  // (u % PPA) * RPU + lt / 4 of plane (tid < NTH/2 ? 0 : NA) + u / PPA (KSP = 2;
+  // lt = tid % (NTH/2)).
   // buffer descriptors of the planes' rows of this tile (unused ones repeat plane 0;
   // plain variables: the host pass drops the kernel if a descriptor is a temporary);
   // the planes hold pad(I) and pad(J) rows, pad = G_BM
   const int ip = (p.I + G_BM - 1) / G_BM * G_BM, jp = (p.J + G_BM - 1) / G_BM * G_BM;
   auto plane_base = [&](int pl) {
-    return pl < NA ? p.A[pl] + (int64_t)i0 * p.ld : p.B[pl - NA] + (int64_t)j0 * p.ld;
+    return pl < NA ? p.A[pl] + (int64_t)i0 * p.ld : p.B[pl - NA] + (BNAT ? 0 : (int64_t)j0 * p.ld);
   };
   auto plane_bytes = [&](int pl) {
-    return (uint32_t)(min(T, pl < NA ? ip - i0 : jp - j0) * p.ld * 2);
+    return (uint32_t)((pl < NA ? min(TI, ip - i0) : min(TJ, jp - j0)) * p.ld * 2);
   };
   const __amdgpu_buffer_rsrc_t rs0 =
       __builtin_amdgcn_make_buffer_rsrc((void*)plane_base(0), 0, plane_bytes(0), 0x00020000);
@@ -292,13 +326,35 @@ __global__ __launch_bounds__(bg_threads<T>(), 1) void bgemm_kernel(BGemm p) {
   static_assert(NA + NB <= 4, "at most four planes");
   const int lt = tid % LTH, lw = lt / 64;  // thread and wave within the loading group
   const uint32_t voff0 = (uint32_t)(((lt / 4) * p.ld + (((lt % 4) ^ ((lt / 16) % 4)) * 8)) * 2);
+  // BNAT: B's chunk as stored, in sub-tiles [TJ / 32][32 k][32 columns] of 64-byte rows:
+  // 16-byte chunk c of the stage's B part holds k (c / 4) % 32, columns 8 (c % 4) .. of
+  // sub-tile c / 128. With SWIGLU the sub-tiles alternate between gate and up (a wave's 64
+  // chunks lie in one sub-tile of fixed parity). Rows past K read as zeros through the
+  // buffer range (the row offset is in the lane's offset: the range check leaves the scalar
+  // offset out); columns past ldb run into the next row and are never stored.
+  const int bw = SWIGLU ? (__builtin_amdgcn_readfirstlane(wid) >> 1) & 1 : 0;
+  const int jcol = SWIGLU ? j0 / 2 : j0;  // first column of this tile in the stored matrix
+  const __bf16* bn = p.B[bw] + jcol;
+  const uint32_t bn_bytes = BNAT ? (uint32_t)(((int64_t)p.K * p.ldb - jcol) * 2) : 0;
+  const __amdgpu_buffer_rsrc_t rsb =
+      __builtin_amdgcn_make_buffer_rsrc((void*)bn, 0, bn_bytes, 0x00020000);
+  const uint32_t voffb =
+      (uint32_t)(((tid >> 2) & 31) * p.ldb + (SWIGLU ? tid >> 8 : tid >> 7) * 32 + (tid & 3) * 8) * 2;
   auto issue = [&](int q, int buf) {
     const uint32_t k0b = (uint32_t)(q * BG_KC * 2);
     static_for<LPT>([&](auto u_t) {
       constexpr int u = decltype(u_t)::value;
-      const uint32_t vo = voff0 + (uint32_t)((u % PPR) * RPU * p.ld * 2);
-      if constexpr (KSP == 1) {
-        constexpr int pl = u / PPR;
+      // KSP = 1: the stacked rows of A's planes, then B's; KSP = 2: one side's planes
+      constexpr bool in_a = u < NA * PPA;
+      constexpr int ur = KSP == 1 && !in_a ? (u - NA * PPA) % PPB : u % PPA;  // round in the plane
+      const uint32_t vo = voff0 + (uint32_t)(ur * RPU * p.ld * 2);
+      if constexpr (BNAT && !in_a) {
+        PKV_LDS void* dst = (PKV_LDS void*)&lds[buf][(u * NTH + wid * 64) * 8];
+        const uint32_t vb = voffb + (uint32_t)((u - NA * PPA) * (SWIGLU ? 2 : 4) * 64) +
+                            (uint32_t)(q * BG_KC) * (uint32_t)(p.ldb * 2);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsb, dst, 16, vb, 0, 0, 0);
+      } else if constexpr (KSP == 1) {
+        constexpr int pl = in_a ? u / PPA : NA + (u - NA * PPA) / PPB;
         PKV_LDS void* dst = (PKV_LDS void*)&lds[buf][(u * NTH + wid * 64) * 8];
         if constexpr (pl == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs0, dst, 16, vo, k0b, 0, 0);
         else if constexpr (pl == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs1, dst, 16, vo, k0b, 0, 0);
@@ -306,14 +362,14 @@ __global__ __launch_bounds__(bg_threads<T>(), 1) void bgemm_kernel(BGemm p) {
         else __builtin_amdgcn_raw_ptr_buffer_load_lds(rs3, dst, 16, vo, k0b, 0, 0);
       } else {
         // a wave's 64 lanes fill 16 rows (1 KB) of one plane; which plane is wave-uniform
-        constexpr int pu = u / PPR;  // plane within the side (hi or lo)
-        const int row = (u % PPR) * RPU + lw * 16;
+        constexpr int pu = u / PPA;  // plane within the side (hi or lo)
+        const int row = (u % PPA) * RPU + lw * 16;
         if (__builtin_amdgcn_readfirstlane(wid) < NTH / 128) {
-          PKV_LDS void* dst = (PKV_LDS void*)&lds[buf][(pu * T + row) * BG_KC];
+          PKV_LDS void* dst = (PKV_LDS void*)&lds[buf][(pu * TI + row) * BG_KC];
           if constexpr (pu == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs0, dst, 16, vo, k0b, 0, 0);
           else __builtin_amdgcn_raw_ptr_buffer_load_lds(rs1, dst, 16, vo, k0b, 0, 0);
         } else {
-          PKV_LDS void* dst = (PKV_LDS void*)&lds[buf][((NA + pu) * T + row) * BG_KC];
+          PKV_LDS void* dst = (PKV_LDS void*)&lds[buf][(NA * TI + pu * TJ + row) * BG_KC];
           if constexpr (pu == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs2, dst, 16, vo, k0b, 0, 0);
           else __builtin_amdgcn_raw_ptr_buffer_load_lds(rs3, dst, 16, vo, k0b, 0, 0);
         }
@@ -328,45 +384,84 @@ __global__ __launch_bounds__(bg_threads<T>(), 1) void bgemm_kernel(BGemm p) {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
   };
   const int sw = (l32 / 4) % 4;
-
-  // chunk q in stage q % S; S - 1 chunks in flight ahead of the one multiplied
+  const int bn_lane = (8 * h32 + ((lane & 15) >> 2)) * 32 + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
+  // the fragments of the 16 k at ks of the chunk in stage st
+  struct Frags {
+    bf16x8 a[NA][MA], b[NB][MB];
+  };
+  auto read = [&](Frags& f, int st, int ks) {
+    const __bf16* L0 = lds[st];
+    const int ch = ((2 * (ks / 16) + h32) ^ sw) * 8;  // k chunk of this lane, swizzled
 #pragma unroll
-  for (int q = 0; q < S - 1; ++q)
-    if (q < nq) issue(q, q);
-  if (S == 3 && nq > 1) landed(std::integral_constant<int, LPT>{});
-  else landed(std::integral_constant<int, 0>{});
-  for (int q = 0; q < nq; ++q) {
-    const int buf = q % S;
-    // the stage of chunk q + S - 1 was last read in step q - 1 (a barrier ago)
-    if (q + S - 1 < nq) issue(q + S - 1, (q + S - 1) % S);
-    const __bf16* L0 = lds[buf];
+    for (int pa = 0; pa < NA; ++pa)
 #pragma unroll
-    for (int kk = 0; kk < BG_KC / KSP; kk += 16) {
-      const int ks = KSP == 1 ? kk : 16 * kh;
-      const int ch = ((2 * (ks / 16) + h32) ^ sw) * 8;  // k chunk of this lane, swizzled
-      bf16x8 fa[NA][MA], fb[NB][MB];
+      for (int a = 0; a < MA; ++a)
+        f.a[pa][a] = *(const bf16x8*)(L0 + (pa * TI + wi + 32 * a + l32) * BG_KC + ch);
 #pragma unroll
-      for (int pa = 0; pa < NA; ++pa)
+    for (int pb = 0; pb < NB; ++pb)
 #pragma unroll
-        for (int a = 0; a < MA; ++a)
-          fa[pa][a] = *(const bf16x8*)(L0 + (pa * T + wi + 32 * a + l32) * BG_KC + ch);
+      for (int b = 0; b < MB; ++b) {
+        if constexpr (BNAT) {
+          // two transposing reads: lane 4 r + q of a 16-lane group points at k row r,
+          // columns 4 q .. of a 4 x 16 block; a half-wave reads 256 contiguous bytes
+          const PKV_LDS __bf16* t = (const PKV_LDS __bf16*)(L0 + NA * TI * BG_KC + (wj / 32 + b) * (32 * 32) +
+                                                            ks * 32 + bn_lane);
+          f.b[pb][b] = cat8(lds_read_tr16(t), lds_read_tr16(t + 4 * 32));
+        } else {
+          f.b[pb][b] = *(const bf16x8*)(L0 + (NA * TI + pb * TJ + wj + 32 * b + l32) * BG_KC + ch);
+        }
+      }
+  };
+  auto mult = [&](const Frags& f) {
 #pragma unroll
-      for (int pb = 0; pb < NB; ++pb)
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int a = 0; a < MA; ++a)
 #pragma unroll
         for (int b = 0; b < MB; ++b)
-          fb[pb][b] = *(const bf16x8*)(L0 + ((NA + pb) * T + wj + 32 * b + l32) * BG_KC + ch);
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int a = 0; a < MA; ++a)
-#pragma unroll
-          for (int b = 0; b < MB; ++b)
-            acc[a][b] = mfma32(fb[(TB >> t) & 1][b], fa[(TA >> t) & 1][a], acc[a][b]);
+          acc[a][b] = mfma32(f.b[(TB >> t) & 1][b], f.a[(TA >> t) & 1][a], acc[a][b]);
+  };
+
+  // Chunk q in stage q % S; S chunks in flight at first. The fragments of the next 16 k are
+  // read while the current ones are multiplied, across the barrier too: the barrier in
+  // the middle of step q says that every wave has read chunk q (its stage takes chunk
+  // q + S) and that chunk q + 1 has landed (the S - 2 chunks after it may be in flight).
+  static_for<S>([&](auto q_t) {
+    if (decltype(q_t)::value < nq) issue(decltype(q_t)::value, decltype(q_t)::value);
+  });
+  if (nq >= S) landed(std::integral_constant<int, (S - 1) * LPT>{});
+  else landed(std::integral_constant<int, 0>{});
+  Frags f[KSP == 1 ? 2 : 1];
+  if constexpr (KSP == 1) read(f[0], 0, 0);
+  auto step = [&](int q, auto st_t, auto tail_t) {
+    constexpr int st = decltype(st_t)::value, sn = (st + 1) % S;
+    constexpr bool TAIL = decltype(tail_t)::value;
+    auto next = [&]() {
+      if (!TAIL || q + S - 1 < nq) landed(std::integral_constant<int, (S - 2) * LPT>{});
+      else landed(std::integral_constant<int, 0>{});
+      if (!TAIL || q + S < nq) issue(q + S, st);
+    };
+    if constexpr (KSP == 1) {
+      read(f[1], st, 16);
+      mult(f[0]);
+      next();
+      // (past the last chunk too, unused: a branch around these reads would make the
+      // products below wait for all of them)
+      read(f[0], sn, 0);
+      mult(f[1]);
+    } else {
+      read(f[0], st, 16 * kh);  // (a second set of fragments would not fit in registers)
+      mult(f[0]);
+      next();
     }
-    // chunk q + 1 has landed (with three stages, chunk q + 2 may still be in flight)
-    if (S == 3 && q + 2 < nq) landed(std::integral_constant<int, LPT>{});
-    else landed(std::integral_constant<int, 0>{});
-  }
+  };
+  int q0 = 0;
+  for (; q0 + 2 * S - 1 < nq; q0 += S)
+    static_for<S>([&](auto s_t) { step(q0 + decltype(s_t)::value, s_t, std::false_type{}); });
+  for (; q0 < nq; q0 += S)
+    static_for<S>([&](auto s_t) {
+      if (q0 + decltype(s_t)::value < nq) step(q0 + decltype(s_t)::value, s_t, std::true_type{});
+    });
   // KSP = 2: the second k half's partial tile goes through the (now idle) stages,
   // lane-major per register (a wave's 64 lanes write and read 256 consecutive bytes),
   // and is added in the epilogue, four values at a time
@@ -386,6 +481,27 @@ __global__ __launch_bounds__(bg_threads<T>(), 1) void bgemm_kernel(BGemm p) {
     if (kh == 1) return;
   }
 
+  if constexpr (SWIGLU) {
+    // column blocks 2 b and 2 b + 1 of the tile hold gate and up of the same 32 features:
+    // H = silu(g) u, silu(g) = g / (1 + e^-g)
+#pragma unroll
+    for (int a = 0; a < MA; ++a)
+#pragma unroll
+      for (int b = 0; b < MB; b += 2)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int i = i0 + wi + 32 * a + l32, j = (j0 + wj + 32 * b) / 2 + 8 * g + 4 * h32;
+          if (i >= p.I || j >= p.J / 2) continue;
+          f32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float x = acc[a][b][4 * g + e];
+            v[e] = x / (1.0f + expf(-x)) * acc[a][b + 1][4 * g + e];
+          }
+          *(f32x4*)(p.Out + (int64_t)i * p.ldo + j) = v;
+        }
+    return;
+  }
   // lane owns Out[i0+wi+32a+l32][j0+wj+32b+8g+4h32 .. +3]
 #pragma unroll
   for (int a = 0; a < MA; ++a)
@@ -432,16 +548,51 @@ __global__ __launch_bounds__(bg_threads<T>(), 1) void bgemm_kernel(BGemm p) {
       }
 }
 
-// symmetric products on 192-tiles, the others on 256-tiles
-template <int NA, int NB, int NT, int TA, int TB, bool SYM>
-hipError_t run_bgemm(BGemm p, hipStream_t st) {
-  constexpr int T = SYM ? 192 : 256;
-  p.tiles_j = (int)((p.J + T - 1) / T);
-  p.ntiles = SYM ? p.tiles_j * (p.tiles_j + 1) / 2 : (int)((p.I + T - 1) / T) * p.tiles_j;
-  p.vec_out = (p.ldo & 3) == 0 && ((uintptr_t)p.Out & 15) == 0;
-  const dim3 grid((p.ntiles + kXcds - 1) / kXcds * kXcds), block(bg_threads<T>());
-  hipLaunchKernelGGL((bgemm_kernel<T, NA, NB, NT, TA, TB, SYM>), grid, block, 0, st, p);
+template <class CFG, int NA, int NB, int NT, int TA, int TB, bool SYM, bool BNAT, bool SWIGLU>
+hipError_t launch_bgemm(BGemm& p, hipStream_t st) {
+  p.tiles_j = (p.J + CFG::TJ - 1) / CFG::TJ;
+  p.ntiles = SYM ? p.tiles_j * (p.tiles_j + 1) / 2 : (p.I + CFG::TI - 1) / CFG::TI * p.tiles_j;
+  const dim3 grid((p.ntiles + kXcds - 1) / kXcds * kXcds), block(CFG::NTH);
+  hipLaunchKernelGGL((bgemm_kernel<CFG, NA, NB, NT, TA, TB, SYM, BNAT, SWIGLU>), grid, block, 0, st, p);
   return hipGetLastError();
+}
+
+// The tile whose rounds over the 256 CUs are estimated shortest: 1, 0.62 and 0.42 are the
+// measured times of one round of 256 x 256, 128 x 256 and 128 x 128 tiles. Targets of
+// d = 4096 with all three (us): M = 1024 223 / 138 / 110, 2048 241 / 173 / 199, 3000
+// 260 / 283 / 282, 4096 323 / 339 / 383; d = 1500, M = 2000 135 / 80 / 56. Symmetric
+// products: 128-tiles while one round of them holds the triangle (d = 1500, M = 2000, G and C:
+// 222 us on large tiles, 100 now), else 192-tiles.
+template <int NA, int NB, int NT, int TA, int TB, bool SYM, bool BNAT = false, bool SWIGLU = false>
+hipError_t run_bgemm(BGemm p, hipStream_t st) {
+  p.vec_out = (p.ldo & 3) == 0 && ((uintptr_t)p.Out & 15) == 0;
+  auto rounds = [&](int ti, int tj) {
+    return ((int64_t)((p.I + ti - 1) / ti) * ((p.J + tj - 1) / tj) + 255) / 256;
+  };
+  using Small = std::conditional_t<SWIGLU, BgCfg<128, 128, 32, 64, 4, 1>, BgCfg<128, 128, 64, 32, 4, 1>>;
+  if constexpr (SYM) {
+    const int64_t t = (p.J + 127) / 128;
+    if (t * (t + 1) / 2 <= 256) return launch_bgemm<Small, NA, NB, NT, TA, TB, true, false, false>(p, st);
+    return launch_bgemm<BgSym, NA, NB, NT, TA, TB, true, false, false>(p, st);
+  } else {
+    using Big = std::conditional_t<NA + NB == 3, BgCfg<256, 256, 64, 128, 3, 1>, BgCfg<256, 256, 128, 64, 2, 1>>;
+    using Mid = BgCfg<128, 256, 64, 64, 3, 1>;
+    const double big = 1.0 * rounds(256, 256), mid = 0.62 * rounds(128, 256), small = 0.42 * rounds(128, 128);
+    if (big <= mid && big <= small) return launch_bgemm<Big, NA, NB, NT, TA, TB, false, BNAT, SWIGLU>(p, st);
+    if (mid <= small) return launch_bgemm<Mid, NA, NB, NT, TA, TB, false, BNAT, SWIGLU>(p, st);
+    return launch_bgemm<Small, NA, NB, NT, TA, TB, false, BNAT, SWIGLU>(p, st);
+  }
+}
+
+// bf16 weights [K][J] that the GEMM reads as stored: 16-byte pieces of whole rows, the
+// matrix within a buffer descriptor's range, and few rows M of the other operand. The
+// transposing reads make the product about 18 % slower, the transposed copies cost the same
+// whatever M is. SwiGLU features of d = 4096, d_ff = 14336, as stored against transposed, us:
+// M = 128 101 / 203, 512 234 / 302, 1024 444 / 496, 1536 653 / 689, 2048 886 / 895,
+// 4096 1678 / 1605; d = 1088, d_ff = 3456, M = 700 48 / 52, 3000 133 / 121.
+constexpr int kStoredRows = 1536;
+bool as_stored(const void* W, int64_t M, int64_t K, int64_t J) {
+  return M <= kStoredRows && J % 8 == 0 && ((uintptr_t)W & 15) == 0 && (K + G_KC) * J * 2 < (int64_t)1 << 32;
 }
 
 hipError_t run_split_rows(const float* S1, const float* S2, int64_t rows, int64_t cols, int64_t ld,
@@ -455,65 +606,93 @@ hipError_t run_split_rows(const float* S1, const float* S2, int64_t rows, int64_
 template <class SRC>
 hipError_t run_split_transpose(const SRC* S1, const float* S2, int64_t rows, int64_t cols,
                                int64_t ld, __bf16* hi, __bf16* lo, int64_t rows_p, int64_t cols_p,
-                               hipStream_t st, float s2 = -1.f) {
-  // rows_p is a multiple of 8 (every caller pads it to 64): whole 16-byte chunks
+                               hipStream_t st, float s2 = -1.f, int pair = -1) {
+  // rows_p is a multiple of 8 (every caller pads it to 64), cols_p of 8: whole 16-byte chunks
+  if constexpr (std::is_same<SRC, __bf16>::value) {
+    if (!S2 && !lo && cols % 8 == 0 && ld % 8 == 0 && (uintptr_t)S1 % 16 == 0) {
+      const dim3 grid((unsigned)((cols_p + 127) / 128), (unsigned)((rows_p + 127) / 128));
+      hipLaunchKernelGGL(transpose_bf16_kernel, grid, dim3(256), 0, st, S1, (int)rows, (int)cols, ld, hi,
+                         (int)rows_p, (int)cols_p, pair);
+      return hipGetLastError();
+    }
+  }
   const dim3 grid((unsigned)((cols_p + 63) / 64), (unsigned)((rows_p + 127) / 128));
   const int vec = ld % 4 == 0 && (uintptr_t)S1 % (4 * sizeof(SRC)) == 0 &&
                   (S2 == nullptr || (uintptr_t)S2 % 16 == 0);
   hipLaunchKernelGGL((split_transpose_kernel<SRC>), grid, dim3(256), 0, st, S1, S2, s2, (int)rows,
-                     (int)cols, ld, hi, lo, (int)rows_p, (int)cols_p, vec);
+                     (int)cols, ld, hi, lo, (int)rows_p, (int)cols_p, vec, pair);
   return hipGetLastError();
 }
 
 // u = z / sqrt(mean(z^2) + eps) per row, split into hi and lo planes [rows_p][cols_p]
-// (zero outside rows x cols). One workgroup per row; the mean square in fp32.
+// (zero outside rows x cols). One workgroup per row; the mean square in fp32. A thread
+// owns 8 consecutive columns of every 2,048; the first kRmsKeep such pieces stay in
+// registers between the two passes. Memory bound:
+// 4096 x 4096 29 us (4.6 TB/s), 55 with scalar loads and a second read of z.
+constexpr int kRmsKeep = 4;
 __global__ __launch_bounds__(256) void rmsnorm_split_kernel(const float* __restrict__ Z, int rows,
                                                             int cols, float eps,
                                                             __bf16* __restrict__ hi,
                                                             __bf16* __restrict__ lo, int cols_p) {
-  __shared__ float part[8];
+  __shared__ float part[5];
   const int r = blockIdx.x, tid = threadIdx.x;
-  float inv = 0.f;
-  if (r < rows) {
-    const float* z = Z + (int64_t)r * cols;
-    float ss = 0.f;
-    for (int c = tid; c < cols; c += 256) ss = fmaf(z[c], z[c], ss);
+  const float* z = Z + (int64_t)r * cols;
+  const bool vec = (cols & 3) == 0 && ((uintptr_t)Z & 15) == 0;
+  auto load = [&](int c0, f32x4 (&v)[2]) {
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
-    if ((tid & 63) == 0) part[tid >> 6] = ss;
-    __syncthreads();
-    if (tid == 0) part[4] = 1.0f / sqrtf((part[0] + part[1] + part[2] + part[3]) / (float)cols + eps);
-    __syncthreads();
-    inv = part[4];
+    for (int h = 0; h < 2; ++h) {
+      const int c = c0 + 4 * h;
+      v[h] = f32x4{};
+      if (r < rows) {
+        if (vec) {
+          if (c < cols) v[h] = *(const f32x4*)(z + c);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (c + e < cols) v[h][e] = z[c + e];
+        }
+      }
+    }
+  };
+  f32x4 keep[kRmsKeep][2], v[2];
+  float ss = 0.f;
+  auto square = [&](const f32x4 (&x)[2]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ss = fmaf(x[e >> 2][e & 3], x[e >> 2][e & 3], ss);
+  };
+#pragma unroll
+  for (int u = 0; u < kRmsKeep; ++u) load(tid * 8 + u * 2048, keep[u]);
+#pragma unroll
+  for (int u = 0; u < kRmsKeep; ++u) square(keep[u]);
+  for (int c0 = tid * 8 + kRmsKeep * 2048; c0 < cols; c0 += 2048) {
+    load(c0, v);
+    square(v);
   }
-  for (int c0 = tid * 8; c0 < cols_p; c0 += 256 * 8) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
+  if ((tid & 63) == 0) part[tid >> 6] = ss;
+  __syncthreads();
+  if (tid == 0) part[4] = 1.0f / sqrtf((part[0] + part[1] + part[2] + part[3]) / (float)cols + eps);
+  __syncthreads();
+  const float inv = r < rows ? part[4] : 0.f;
+  auto store = [&](int c0, const f32x4 (&x)[2]) {
+    if (c0 >= cols_p) return;
     bf16x8 h, l;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int c = c0 + e;
-      const float v = (r < rows && c < cols) ? Z[(int64_t)r * cols + c] * inv : 0.f;
-      h[e] = to_bf16(v);
-      l[e] = to_bf16(v - (float)h[e]);
+      const float u = x[e >> 2][e & 3] * inv;
+      h[e] = to_bf16(u);
+      l[e] = to_bf16(u - (float)h[e]);
     }
     *(bf16x8*)(hi + (int64_t)r * cols_p + c0) = h;
     *(bf16x8*)(lo + (int64_t)r * cols_p + c0) = l;
-  }
-}
-
-// H[m][j] = silu(GU[m][j]) * GU[m][up + j], silu(g) = g / (1 + e^-g), for j < d_ff.
-__global__ __launch_bounds__(256) void swiglu_kernel(const float* __restrict__ GU, int64_t ldgu,
-                                                     int64_t up, int rows, int d_ff,
-                                                     float* __restrict__ H) {
-  const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int per_row = d_ff / 4;
-  if (g >= (int64_t)rows * per_row) return;
-  const int r = (int)(g / per_row), j = (int)(g % per_row) * 4;
-  const f32x4 a = *(const f32x4*)(GU + (int64_t)r * ldgu + j);
-  const f32x4 b = *(const f32x4*)(GU + (int64_t)r * ldgu + up + j);
-  f32x4 h;
+  };
 #pragma unroll
-  for (int e = 0; e < 4; ++e) h[e] = a[e] / (1.0f + expf(-a[e])) * b[e];
-  *(f32x4*)(H + (int64_t)r * d_ff + j) = h;
+  for (int u = 0; u < kRmsKeep; ++u) store(tid * 8 + u * 2048, keep[u]);
+  for (int c0 = tid * 8 + kRmsKeep * 2048; c0 < cols_p; c0 += 2048) {
+    load(c0, v);
+    store(c0, v);
+  }
 }
 
 struct TargetsWs {
@@ -546,20 +725,19 @@ NormalEqWs normal_eq_layout(int64_t rows, int64_t din, int64_t dout) {
 }
 
 struct MlpWs {
-  size_t Uh, Ul, Wh, Wl, GU, total;
-  int64_t Mp, Kp, Jh;  // padded rows, padded d, padded d_ff (one half of the gate|up planes)
+  size_t Uh, Ul, Wh, Wl, total;
+  int64_t Mp, Kp, Jh;  // padded rows, padded d, padded d_ff (half of the interleaved gate and up rows)
 };
 MlpWs mlp_layout(int64_t M, int64_t d, int64_t d_ff) {
   MlpWs L{};
   L.Mp = pad_to(M, G_BM);
   L.Kp = pad_to(d, G_KC);
-  L.Jh = pad_to(d_ff, G_BM);
+  L.Jh = pad_to(d_ff, G_BM / 2);
   size_t o = 0;
   L.Uh = o; o += align_up((size_t)L.Mp * L.Kp * 2);
   L.Ul = o; o += align_up((size_t)L.Mp * L.Kp * 2);
   L.Wh = o; o += align_up((size_t)2 * L.Jh * L.Kp * 2);
   L.Wl = o; o += align_up((size_t)2 * L.Jh * L.Kp * 2);
-  L.GU = o; o += align_up((size_t)M * 2 * L.Jh * 4);
   L.total = o;
   return L;
 }
@@ -655,39 +833,39 @@ hipError_t launch_mlp_features(const float* Z, const void* Wg, const void* Wu, b
   char* w = (char*)ws;
   __bf16 *Uh = (__bf16*)(w + L.Uh), *Ul = (__bf16*)(w + L.Ul);
   __bf16 *Wh = (__bf16*)(w + L.Wh), *Wl = (__bf16*)(w + L.Wl);
-  float* GU = (float*)(w + L.GU);
   hipLaunchKernelGGL(rmsnorm_split_kernel, dim3((unsigned)L.Mp), dim3(256), 0, st, Z, (int)M, (int)d,
                      eps, Uh, Ul, (int)L.Kp);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // [Wg | Wu] transposed: rows [0, d_ff) gate, rows [Jh, Jh + d_ff) up
-  const int64_t off = L.Jh * L.Kp;
+  // gate and up interleaved in blocks of 32 features, so a workgroup's tile holds both of
+  // a feature and forms H itself
+  BGemm p{};
+  p.ld = L.Kp;
+  p.Out = H;
+  p.ldo = d_ff;
+  p.I = (int)M;
+  p.J = (int)(2 * d_ff);
+  p.Kp = (int)L.Kp;
+  p.A[0] = Uh; p.A[1] = Ul;
+  if (w_bf16 && as_stored(Wg, M, d, d_ff) && as_stored(Wu, M, d, d_ff)) {
+    p.B[0] = (const __bf16*)Wg; p.B[1] = (const __bf16*)Wu;
+    p.ldb = d_ff;
+    p.K = (int)d;
+    return run_bgemm<2, 1, 2, 0b10, 0b00, false, true, true>(p, st);
+  }
   for (int h = 0; h < 2; ++h) {
     const void* Wx = h ? Wu : Wg;
     if (w_bf16)
-      e = run_split_transpose((const __bf16*)Wx, nullptr, d, d_ff, d_ff, Wh + h * off, nullptr, L.Kp,
-                              L.Jh, st);
+      e = run_split_transpose((const __bf16*)Wx, nullptr, d, d_ff, d_ff, Wh, nullptr, L.Kp, L.Jh, st,
+                              -1.f, 32 * h);
     else
-      e = run_split_transpose((const float*)Wx, nullptr, d, d_ff, d_ff, Wh + h * off,
-                              Wl + h * off, L.Kp, L.Jh, st);
+      e = run_split_transpose((const float*)Wx, nullptr, d, d_ff, d_ff, Wh, Wl, L.Kp, L.Jh, st, -1.f,
+                              32 * h);
     if (e != hipSuccess) return e;
   }
-  BGemm p{};
-  p.ld = L.Kp;
-  p.Out = GU;
-  p.ldo = 2 * L.Jh;
-  p.I = (int)M;
-  p.J = (int)(2 * L.Jh);
-  p.Kp = (int)L.Kp;
-  p.A[0] = Uh; p.A[1] = Ul;
   p.B[0] = Wh; p.B[1] = Wl;
-  e = w_bf16 ? run_bgemm<2, 1, 2, 0b10, 0b00, false>(p, st)
-             : run_bgemm<2, 2, 3, 0b010, 0b100, false>(p, st);
-  if (e != hipSuccess) return e;
-  const int64_t n = M * (d_ff / 4);
-  hipLaunchKernelGGL(swiglu_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, GU, 2 * L.Jh,
-                     L.Jh, (int)M, (int)d_ff, H);
-  return hipGetLastError();
+  return w_bf16 ? run_bgemm<2, 1, 2, 0b10, 0b00, false, false, true>(p, st)
+                : run_bgemm<2, 2, 3, 0b010, 0b100, false, false, true>(p, st);
 }
 
 size_t propagate_ws_bytes(int64_t M, int64_t d_ff, int64_t d) {
