@@ -3,6 +3,7 @@
 // check and the fixed scratch of the allocation-free entry point.
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "attention_kernels.hpp"
@@ -71,12 +72,20 @@ AttnPlan plan_attention(const AttnShape& s) {
   // one bf16 tile-iteration of a workgroup ~ 64 x rows x dh x 4 flops at ~4 TFLOP/s per CU
   // (shared by the workgroups resident on the CU)
   const double tile_s = (double)kt * rows_wg * s.dh * 4.0 / (s.bf16 ? 4e12 / kWgPerCu : 0.45e12);
+  // own entries (tiles of a row tile's causal prefix, longest and on average): work items
+  // of a short cache differ in length and are handed out longest first, which takes about
+  // the total over the CUs plus half of a shortest item; where the cache range is the
+  // longer part they run in rounds
+  const int64_t own_max = (s.Ms + kt - 1) / kt;
   double best = 1e300;
   int best_s = 1;
   for (int sp = 1; sp <= 64 && sp <= ntiles; ++sp) {
     const int64_t tps = (ntiles + sp - 1) / sp;
     const int64_t waves = (items * sp + (int64_t)slots - 1) / (int64_t)slots;
     double cost = (double)waves * tps * tile_s;
+    if (s.bf16 && tps < own_max)
+      cost = tile_s * std::max((double)items * (ntiles + 0.5 * own_max) / slots + 0.5 * tps,
+                               (double)(tps + own_max));
     if (sp > 1) cost += (double)s.Hkv * rows * (s.dh + 2) * 4.0 * sp * 2 / 4e12 + 4e-6;
     if (cost < best * 0.98) {
       best = cost;

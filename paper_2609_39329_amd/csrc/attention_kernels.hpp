@@ -86,6 +86,7 @@ struct AttnParams {
   int rows;
   int row_tiles;
   int total_items, per_xcd;
+  int order;  // bf16 path: how workgroups map to work items (kOrder..., see work_item)
   float c;  // bf16: scale * log2(e); f32: scale
   // own entries of a reference chunk (OWN kernels): Ks, Vs [Hkv][Ms][dh]; Vts their
   // V^T tiles (bf16)
@@ -223,6 +224,91 @@ __global__ __launch_bounds__(256) void vt_kernel(const void* __restrict__ V,
   }
 }
 
+// Work items of unequal length (a chunk's own prefix grows with the row tile; per-head index
+// sets differ between heads) are handed out longest first, each XCD the same mix, so the
+// CUs finish together: the hardware takes workgroups in order, workgroup b on XCD b % 8.
+// With items in row order and a head per XCD, the last items were the longest and the
+// XCD of the longest head finished last (4,096 queries, 8 heads of 1,720 entries on
+// average: 222 -> 179 us; a 5,120-token chunk over 1,720 entries: 627 -> 570 us, both with the
+// steps past the last tile left out).
+//   kOrderRows (equal items): runs of row tiles of one head per XCD, as its L2 likes it.
+//   kOrderOwn (own entries): last key range and last row tiles first; a head's row tiles
+//     stay on its XCD (Hkv a multiple of 8) or are dealt to its XCDs (a divisor of 8).
+//   kOrderCounts (per-head counts): heads by falling count, every head on every XCD.
+constexpr int kOrderRows = 0, kOrderOwn = 1, kOrderCounts = 2;
+struct WorkItem {
+  int g, split, rt;  // KV head, key range, row tile (rt < 0: none)
+};
+
+// the head of rank k by falling count (ties: lower head first); heads <= 64, whole wave
+__device__ __forceinline__ int head_of_rank(const int32_t* counts, int heads, int Nk, int k) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int mine = lane < heads ? min(max(counts[lane], 1), Nk) : 0;
+  int rank = 0;
+  for (int h = 0; h < heads; ++h) {
+    const int c = __builtin_amdgcn_readlane(mine, h);
+    rank += (c > mine || (c == mine && h < lane)) ? 1 : 0;
+  }
+  const uint64_t hit = __ballot(lane < heads && rank == k);
+  return (int)__builtin_ctzll(hit);
+}
+
+// workgroups per XCD
+__host__ __device__ inline int order_per_xcd(int order, int heads, int row_tiles, int n_split, int per_xcd) {
+  if (order == kOrderOwn && heads % kXcds == 0) return heads / kXcds * row_tiles * n_split;
+  if (order == kOrderOwn && kXcds % heads == 0) {
+    const int nx = kXcds / heads;
+    return (row_tiles + nx - 1) / nx * n_split;
+  }
+  return per_xcd;
+}
+
+template <bool OWN>
+__device__ __forceinline__ WorkItem work_item(const AttnParams& p) {
+  const int heads = p.Hq / p.G, x = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
+  WorkItem it{0, 0, -1};
+  if (p.order == kOrderRows) {
+    const int w = x * p.per_xcd + i;
+    if (w < p.total_items) {
+      it.rt = w % p.row_tiles;
+      const int t2 = w / p.row_tiles;
+      it.split = t2 % p.n_split;
+      it.g = t2 / p.n_split;
+    }
+    return it;
+  }
+  if (OWN && p.order == kOrderOwn && heads % kXcds == 0) {
+    const int hx = heads / kXcds, q = i / hx;
+    it.g = x * hx + i % hx;
+    it.split = p.n_split - 1 - q / p.row_tiles;
+    it.rt = it.split < 0 ? -1 : p.row_tiles - 1 - q % p.row_tiles;
+    return it;
+  }
+  if (OWN && p.order == kOrderOwn && kXcds % heads == 0) {
+    const int nx = kXcds / heads, nb = (p.row_tiles + nx - 1) / nx;
+    it.g = x / nx;
+    it.split = p.n_split - 1 - i / nb;
+    it.rt = it.split < 0 ? -1 : p.row_tiles - 1 - (i % nb * nx + x % nx);
+    return it;
+  }
+  const int slot = i * kXcds + x;
+  if (slot >= p.total_items) return it;
+  int rank;
+  if (OWN) {
+    rank = slot % heads;
+    const int q = slot / heads;
+    it.rt = p.row_tiles - 1 - q % p.row_tiles;
+    it.split = p.n_split - 1 - q / p.row_tiles;
+  } else {
+    it.rt = slot % p.row_tiles;
+    const int q = slot / p.row_tiles;
+    rank = q % heads;
+    it.split = q / heads;
+  }
+  it.g = p.order == kOrderCounts ? head_of_rank(p.counts, heads, p.Nk, rank) : rank;
+  return it;
+}
+
 // SAFE = false (fast path): each row's exponent offset is fixed to the exact max of
 // its first key tile, so O is never rescaled and only MFMA touches it, and the
 // steady-state loop takes no row maxima at all. Every weight P a lane adds is at most
@@ -277,15 +363,15 @@ __global__ __launch_bounds__(kThreadsBf16, kWgPerCu) void attn_bf16_kernel(AttnP
 
   // work-item coordinates are workgroup-uniform; readfirstlane keeps them (and the
   // buffer descriptors and offsets built from them) in scalar registers
-  const int w = __builtin_amdgcn_readfirstlane(xcd_item(p.per_xcd));
-  if (w >= p.total_items) return;
+  const WorkItem item = work_item<OWN>(p);
+  const int rt = __builtin_amdgcn_readfirstlane(item.rt);
+  if (rt < 0) return;
+  const int split = __builtin_amdgcn_readfirstlane(item.split);
+  const int g = __builtin_amdgcn_readfirstlane(item.g);
+  const int w = __builtin_amdgcn_readfirstlane((g * p.n_split + split) * p.row_tiles + rt);
   if constexpr (SAFE) {
     if (p.flags[w] == 0) return;
   }
-  const int rt = __builtin_amdgcn_readfirstlane(w % p.row_tiles);
-  const int t2 = __builtin_amdgcn_readfirstlane(w / p.row_tiles);
-  const int split = __builtin_amdgcn_readfirstlane(t2 % p.n_split);
-  const int g = __builtin_amdgcn_readfirstlane(t2 / p.n_split);
   // entries of this KV head's cache (a per-head index set may keep fewer than Nk)
   const int nk = p.counts ? __builtin_amdgcn_readfirstlane(min(max(p.counts[g], 1), p.Nk)) : p.Nk;
   const int k_begin = split * p.keys_per_split;
@@ -875,6 +961,8 @@ __global__ __launch_bounds__(kThreadsBf16, kWgPerCu) void attn_bf16_kernel(AttnP
     auto steps = [&](auto masked_t, int t) {
       static_for<NSL / 2>([&](auto h_t) {
         constexpr int H = decltype(h_t)::value;
+        // no steps past the last tile (their tiles would be fully masked)
+        if (decltype(masked_t)::value && H > 0 && t + 2 * H >= ntiles) return;
         step(std::integral_constant<int, 2 * H>{}, masked_t, sa, sb, t + 2 * H);
         step(std::integral_constant<int, 2 * H + 1>{}, masked_t, sb, sa, t + 2 * H + 1);
       });
@@ -1320,6 +1408,8 @@ hipError_t run_attention(const AttnShape& s, const AttnPlan& pl, AttnParams& p, 
   const bool vnat = KQ == 0 && s.bf16 && !gather && !bias && !p.counts && p.src_rows == p.Nk;
   dim3 grid(pl.grid), block(256);
   if (s.bf16) {
+    p.order = p.counts && s.Hkv <= kWave ? kOrderCounts : own ? kOrderOwn : kOrderRows;
+    grid = dim3(order_per_xcd(p.order, s.Hkv, pl.row_tiles, pl.n_split, pl.per_xcd) * kXcds);
     const dim3 vg((unsigned)p.vt_tiles, (unsigned)s.Hkv);
     if (gather)
       hipLaunchKernelGGL((vt_kernel<DH, true, KQ>), vg, block, 0, st, p.V, p.Ve, p.idx,

@@ -1,0 +1,68 @@
+"""Work items handed out longest first (per-head counts; a chunk's own prefix): every row
+tile, key range and head is computed exactly once for head counts that are multiples of
+the 8 XCDs, divisors of them and neither, against fp64 softmax attention.
+
+Two-term P: 5e-5 of the result's norm, as the compressed pass's other tests."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2609_39329_amd as pkv
+from gpu_util import DEV, host, rel
+
+pytestmark = pytest.mark.gpu
+
+
+def normal(seed, *shape):
+    g = torch.Generator().manual_seed(seed)
+    return torch.randn(shape, generator=g).bfloat16().to(DEV)
+
+
+def attend(q, k, v, own=None):
+    s = q @ k.T / np.sqrt(q.shape[1])
+    if own is not None:
+        so = q @ own[0].T / np.sqrt(q.shape[1])
+        so[np.triu_indices(len(q), 1)] = -np.inf
+        s, v = np.concatenate([s, so], 1), np.concatenate([v, own[1]])
+    w = np.exp(s - s.max(1, keepdims=True))
+    return (w / w.sum(1, keepdims=True)) @ v
+
+
+@pytest.mark.parametrize("Hq,Hkv,M", [(16, 16, 300), (8, 8, 513), (8, 4, 700), (6, 2, 200),
+                                      (7, 7, 300), (12, 3, 150), (5, 1, 170)])
+@pytest.mark.parametrize("counts", [False, True])
+@pytest.mark.parametrize("own", [False, True])
+def test_every_item_once(Hq, Hkv, M, counts, own):
+    print(f"order Hq={Hq} Hkv={Hkv} M={M} counts={counts} own={own}", flush=True)
+    dh, N, B = 64, 700, 333
+    rng = np.random.default_rng(Hq + M)
+    Q, K, V = normal(1, M, Hq, dh), normal(2, Hkv, N, dh), normal(3, Hkv, N, dh)
+    Ks, Vs = normal(4, Hkv, M, dh), normal(5, Hkv, M, dh)
+    idx = np.stack([rng.permutation(N)[:B] for _ in range(Hkv)]).astype(np.int32)
+    cnt = rng.integers(1, B + 1, size=Hkv).astype(np.int32) if counts else np.full(Hkv, B, np.int32)
+    kw = dict(idx=torch.from_numpy(idx).to(DEV), counts=torch.from_numpy(cnt).to(DEV) if counts else None)
+    if own:
+        got = pkv.attend_chunk(Q, K, V, Ks, Vs, p_terms=2, **kw)
+    else:
+        got = pkv.attend_compressed(Q, K, V, **kw)
+    got = host(got).reshape(M, Hq, dh)
+    q, k, v, ks, vs = (host(t) for t in (Q, K, V, Ks, Vs))
+    for h in range(Hq):
+        g = h // (Hq // Hkv)
+        use = idx[g, :cnt[g]]
+        ref = attend(q[:, h], k[g, use], v[g, use], (ks[g], vs[g]) if own else None)
+        assert rel(got[:, h], ref) <= 5e-5, h
+
+
+def test_chunk_prefix_longer_than_the_cache():
+    """A chunk whose own prefix is most of the work: whole own tiles below the diagonal run
+    unmasked, the last ones masked; scores outgrowing the first tile at the diagonal."""
+    M, dh, N = 1100, 128, 40
+    Q, K, V = normal(1, M, 4, dh), normal(2, 1, N, dh), normal(3, 1, N, dh)
+    Ks, Vs = normal(4, 1, M, dh), normal(5, 1, M, dh)
+    for gain in (1.0, 12.0):
+        k_own = (Ks.float() * gain).bfloat16()
+        got = host(pkv.attend_chunk(Q, K, V, k_own, Vs, p_terms=2)).reshape(M, 4, dh)
+        q, k, v, ks, vs = (host(t) for t in (Q, K, V, k_own, Vs))
+        for h in range(4):
+            assert rel(got[:, h], attend(q[:, h], k[0], v[0], (ks[0], vs[0]))) <= 5e-5, (gain, h)
