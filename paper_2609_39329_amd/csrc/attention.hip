@@ -103,7 +103,6 @@ AttnPlan plan_attention(const AttnShape& s) {
                           align_up((size_t)s.Hkv * pl.n_split * rows * 2 * sizeof(float))
                     : 0;
   if (s.bf16) {
-    pl.ws_bytes += align_up((size_t)pl.total_items * sizeof(int));
     pl.ws_bytes += align_up((size_t)s.Hkv * ntiles * 32 * s.dh * 2);  // V^T tiles
     if (s.Ms > 0)  // V^T tiles of the own entries
       pl.ws_bytes += align_up((size_t)s.Hkv * ((s.Ms + kKeyTile - 1) / kKeyTile) * 32 * s.dh * 2);
@@ -143,8 +142,6 @@ hipError_t launch_attention(const AttnShape& s, const void* Q, const void* K, co
   }
   const int64_t vt_tiles = (s.Nk + kKeyTile - 1) / kKeyTile;
   if (s.bf16) {
-    p.flags = (int*)((char*)ws + off);
-    off += align_up((size_t)pl.total_items * sizeof(int));
     p.Vt = (const __bf16*)((char*)ws + off);  // V^T tiles of the cache
     p.vt_tiles = (int)vt_tiles;
     if (s.Ms > 0) {  // then those of the chunk's own entries

@@ -24,7 +24,7 @@
 // register staging; issued by waves 0-3 only), six tiles ahead, with XOR-swizzled
 // 16-byte chunks in place of row padding and one barrier per two tiles (also with a
 // two-term P; block-scaled and gathered keys come through registers into the same
-// slots, V^T by DMA); the biased variants and the fixup stage through registers into
+// slots, V^T by DMA); the biased variants and the rescaled pass stage through registers into
 // four padded slots. The workgroup -> work-item
 // map keeps all row tiles of one KV head (and key range) on one XCD so its L2
 // serves the K/V re-reads.
@@ -77,7 +77,6 @@ struct AttnParams {
   float* O;
   float* Opart;
   float* ML;
-  int* flags;  // bf16 path: per work item, 1 = the fast path left it to the fixup
   int Hq, G;
   int64_t src_rows;
   int src_valid;
@@ -106,7 +105,7 @@ struct AttnParams {
 
 namespace {
 
-constexpr float kTau = 8.0f;   // lazy-rescale threshold of the fixup path (log2 units)
+constexpr float kTau = 8.0f;   // lazy-rescale threshold of the rescaled pass (log2 units)
 constexpr float kBigSum = 0x1p64f;  // fast path: largest trusted partial row sum (2^kBig, kBig = 64)
 
 // A partial row sum the fast path cannot trust: above kBigSum, infinite or NaN (an
@@ -134,7 +133,6 @@ constexpr int kF32Waves = 8;  // f32 path: waves per workgroup (32 rows each)
 // bf16 fast path without gather, bias or two-term P: K / V^T tiles are loaded straight
 // into LDS (buffer_load ... lds) through kDmaSlots slots, each tile's loads issued
 // kDmaAhead steps before the step that scores it, one barrier per kDmaSteps steps
-constexpr bool kAttnDma = true;
 constexpr int kDmaSlots = 8, kDmaAhead = 6, kDmaSteps = 2;
 static_assert(kDmaAhead <= kDmaSlots - kDmaSteps && kDmaAhead >= kDmaSteps + 1,
               "a slot is refilled only after its last read");
@@ -309,23 +307,21 @@ __device__ __forceinline__ WorkItem work_item(const AttnParams& p) {
   return it;
 }
 
-// SAFE = false (fast path): each row's exponent offset is fixed to the exact max of
+// Fast path: each row's exponent offset is fixed to the exact max of
 // its first key tile, so O is never rescaled and only MFMA touches it, and the
 // steady-state loop takes no row maxima at all. Every weight P a lane adds is at most
 // that lane's partial row sum, so a row whose partial sums all stay at or below
 // 2^kBig never met a score more than about kBig (log2 units) above its offset: P, l and O stay far from fp32
 // overflow. A work item with a larger (or non-finite) partial sum in any row is
-// marked in p.flags at the end and its outputs are not trusted. SAFE = true (fixup,
-// launched right after on the same stream): the lazy-rescale online softmax, run
-// only for marked work items, overwriting their outputs.
+// computed again by the same workgroup, as a lazily rescaled online softmax. (As a
+// second launch that found nothing to do, this check cost every call 4 to 5 us.)
 // KQ = 8 or 4: K holds block-scaled integers (exponents in p.Ke), loaded as such and
 // expanded to bf16 when the tile is stored to LDS (through registers on either
 // pipeline); V was expanded by vt_kernel into the V^T tiles.
 // VNAT (contiguous bf16 cache, every row of it used; own entries, if any, as stored):
 // no V^T tiles; V tiles arrive in their stored [key][d] order and the P V product reads
 // its V operand with transposing LDS reads (see vfrag).
-template <int DH, bool GATHER, bool PSPLIT, bool PARTIAL, bool SAFE, bool OWN, bool BIAS, int KQ,
-          bool VNAT>
+template <int DH, bool GATHER, bool PSPLIT, bool PARTIAL, bool OWN, bool BIAS, int KQ, bool VNAT>
 __global__ __launch_bounds__(kThreadsBf16, kWgPerCu) void attn_bf16_kernel(AttnParams p) {
   static_assert(!(OWN && BIAS), "own entries carry no bias");
   static_assert(KQ == 0 || KQ == 8 || KQ == 4, "bf16, int8 or int4 keys");
@@ -346,7 +342,7 @@ __global__ __launch_bounds__(kThreadsBf16, kWgPerCu) void attn_bf16_kernel(AttnP
   // tiles straight into LDS (no register staging), through kDmaSlots unpadded slots
   // whose 16-byte chunks are XOR-swizzled so that the MFMA operand reads stay
   // conflict-free
-  constexpr bool DMA = kAttnDma && !SAFE && !BIAS;
+  constexpr bool DMA = !BIAS;
   // K through registers on the DMA pipeline: block-scaled values, or gathered rows
   constexpr bool KREG = KQ != 0 || GATHER;
   // stored K rows: bf16, or int8 / packed int4 values (KRB bytes per row, KCB bytes per
@@ -354,10 +350,16 @@ __global__ __launch_bounds__(kThreadsBf16, kWgPerCu) void attn_bf16_kernel(AttnP
   constexpr int KCB = KQ ? KQ : 16;
   constexpr int KRB = CH * KCB;
   constexpr int NSL = kDmaSlots;
-  __shared__ __attribute__((aligned(16))) __bf16 Ks[DMA ? 1 : 4][KT * KP];
-  __shared__ __attribute__((aligned(16))) __bf16 Vs[DMA ? 1 : 4][DH * VTP];
-  __shared__ __attribute__((aligned(16))) __bf16 Kd[DMA ? NSL : 1][DMA ? KT * DH : 8];
-  __shared__ __attribute__((aligned(16))) __bf16 Vd[DMA ? NSL : 1][DMA ? DH * KT : 8];
+  // DMA: eight unpadded K and eight V slots; else four padded ones of each. The rescaled
+  // pass of either uses two padded ones in the same memory.
+  constexpr int KBUF = DMA ? NSL * KT * DH : 4 * KT * KP, VBUF = DMA ? NSL * DH * KT : 4 * DH * VTP;
+  static_assert(KBUF >= 2 * KT * KP && VBUF >= 2 * DH * VTP, "two padded slots");
+  __shared__ __attribute__((aligned(16))) __bf16 kbuf[KBUF];
+  __shared__ __attribute__((aligned(16))) __bf16 vbuf[VBUF];
+  __bf16(*const Ks)[KT * KP] = (__bf16(*)[KT * KP])kbuf;
+  __bf16(*const Vs)[DH * VTP] = (__bf16(*)[DH * VTP])vbuf;
+  __bf16(*const Kd)[KT * DH] = (__bf16(*)[KT * DH])kbuf;
+  __bf16(*const Vd)[DH * KT] = (__bf16(*)[DH * KT])vbuf;
   __shared__ __attribute__((aligned(16))) float Bs[BIAS ? 4 : 1][BIAS ? KT : 4];
   __shared__ int overflow;
 
@@ -368,10 +370,6 @@ __global__ __launch_bounds__(kThreadsBf16, kWgPerCu) void attn_bf16_kernel(AttnP
   if (rt < 0) return;
   const int split = __builtin_amdgcn_readfirstlane(item.split);
   const int g = __builtin_amdgcn_readfirstlane(item.g);
-  const int w = __builtin_amdgcn_readfirstlane((g * p.n_split + split) * p.row_tiles + rt);
-  if constexpr (SAFE) {
-    if (p.flags[w] == 0) return;
-  }
   // entries of this KV head's cache (a per-head index set may keep fewer than Nk)
   const int nk = p.counts ? __builtin_amdgcn_readfirstlane(min(max(p.counts[g], 1), p.Nk)) : p.Nk;
   const int k_begin = split * p.keys_per_split;
@@ -385,9 +383,6 @@ __global__ __launch_bounds__(kThreadsBf16, kWgPerCu) void attn_bf16_kernel(AttnP
     // a key range past the end of a shorter head's cache (and without own entries):
     // an empty partial result, weight zero in the merge
     if (ct == 0 && !own_range) {
-      if constexpr (!SAFE) {
-        if (threadIdx.x == 0) p.flags[w] = 0;
-      }
       for (int i = threadIdx.x; i < kRowsBf16; i += blockDim.x) {
         const int r = rt * kRowsBf16 + i;
         if (r >= p.rows) break;
@@ -969,15 +964,30 @@ __global__ __launch_bounds__(kThreadsBf16, kWgPerCu) void attn_bf16_kernel(AttnP
     };
     const int t_full = (k_end - k_begin) / KT;
     int t = 0;
-    for (; t + NSL < t_full; t += NSL) steps(std::false_type{}, t);
-    for (; t < ntiles; t += NSL) steps(std::true_type{}, t);
+    if constexpr (OWN) {
+      // own tiles [ct, own_plain) are visible to every query of the workgroup, so they run
+      // unmasked like the cache's whole tiles (5,120-token chunk over 1,720 entries: 565 ->
+      // 508 us)
+      const int own_plain = own_range ? ct + (rt * kRowsBf16 / p.G + 1) / KT : 0;
+#pragma unroll 1
+      for (int part = 0; part < 2; ++part) {
+        // the cache's whole tiles, its last tile, the own tiles below the diagonal, the rest
+        const int plain = part == 0 ? t_full : own_plain;
+        const int end = part == 0 && own_plain > ct ? ct - 1 : ntiles;
+        for (; t + NSL < plain; t += NSL) steps(std::false_type{}, t);
+        for (; t < end; t += NSL) steps(std::true_type{}, t);
+      }
+    } else {
+      for (; t + NSL < t_full; t += NSL) steps(std::false_type{}, t);
+      for (; t < ntiles; t += NSL) steps(std::true_type{}, t);
+    }
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) over |= untrusted_sum(l_part[qt]);
     if (__ballot(over) != 0) overflow = 1;
     // every load has landed before the slots are given up
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-  } else if constexpr (!SAFE) {
+  } else {
     // Software pipeline over four LDS slots (tile t in slot t % 4) and NSET register
     // staging sets (tile j is loaded into set j % NSET). Step t:
     //   issue the loads of tile t + NSET + 1;
@@ -1044,10 +1054,22 @@ __global__ __launch_bounds__(kThreadsBf16, kWgPerCu) void attn_bf16_kernel(AttnP
     for (int qt = 0; qt < QT; ++qt) over |= untrusted_sum(l_part[qt]);
     if (__ballot(over) != 0) overflow = 1;
     __syncthreads();
-  } else {
-    // lazy rescale: when a row's running max would grow by more than 2^kTau the
-    // wave rescales O first (m_run = -inf on the first tile: alpha = 0)
+  }
+
+  if (overflow) {
+    // lazy rescale, from the start: when a row's running max would grow by more than
+    // 2^kTau the wave rescales O first (m_run = -inf on the first tile: alpha = 0)
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+#pragma unroll
+      for (int dt = 0; dt < ND; ++dt) o[qt][dt] = f32x16{};
+      m_run[qt] = -INFINITY;
+      l_part[qt] = 0.f;
+    }
+    load_tile(0);
+    store_tile(0);
     __syncthreads();
+#pragma unroll 1
     for (int t = 0; t < ntiles; ++t) {
       const int cur = t & 1;
       if (t + 1 < ntiles) load_tile(t + 1);
@@ -1108,9 +1130,6 @@ __global__ __launch_bounds__(kThreadsBf16, kWgPerCu) void attn_bf16_kernel(AttnP
         p.ML[2 * rid + 1] = l;
       }
     }
-  }
-  if constexpr (!SAFE) {
-    if (tid == 0) p.flags[w] = overflow;
   }
 }
 
@@ -1392,7 +1411,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
   *((f32x4*)(O + ((int64_t)m * Hq + g * G + j) * DH) + c4) = acc * (1.0f / l);
 }
 
-// The V^T pre-pass (bf16), the kernels (fast path then fixup, or the f32 kernel) and,
+// The V^T pre-pass (bf16), the kernel (bf16 or f32) and,
 // with split key ranges, the merge. p is complete (plan fields, buffers, Vt / Vts
 // workspace pointers). KQ = 8 or 4 (bf16 only, no own entries): block-scaled K / V.
 // A contiguous bf16 cache without bias or per-head counts, whose every row is an entry,
@@ -1427,17 +1446,10 @@ hipError_t run_attention(const AttnShape& s, const AttnPlan& pl, AttnParams& p, 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const dim3 bblock(kThreadsBf16);
-    // fast path, then the lazy-rescale fixup for any work item it handed back
-#define PKV_LB(G_, P_, S_, O_, B_)                                                                           \
-  do {                                                                                                       \
-    hipLaunchKernelGGL((attn_bf16_kernel<DH, G_, P_, S_, false, O_, B_, KQ, false>), grid, bblock, 0, st, p); \
-    hipLaunchKernelGGL((attn_bf16_kernel<DH, G_, P_, S_, true, O_, B_, KQ, false>), grid, bblock, 0, st, p);  \
-  } while (0)
-#define PKV_LV(P_, S_, O_)                                                                                 \
-  do {                                                                                                     \
-    hipLaunchKernelGGL((attn_bf16_kernel<DH, false, P_, S_, false, O_, false, 0, true>), grid, bblock, 0, st, p); \
-    hipLaunchKernelGGL((attn_bf16_kernel<DH, false, P_, S_, true, O_, false, 0, true>), grid, bblock, 0, st, p);  \
-  } while (0)
+#define PKV_LB(G_, P_, S_, O_, B_) \
+  hipLaunchKernelGGL((attn_bf16_kernel<DH, G_, P_, S_, O_, B_, KQ, false>), grid, bblock, 0, st, p)
+#define PKV_LV(P_, S_, O_) \
+  hipLaunchKernelGGL((attn_bf16_kernel<DH, false, P_, S_, O_, false, 0, true>), grid, bblock, 0, st, p)
 #define PKV_L(G_, P_, S_, O_)                      \
   do {                                             \
     if (bias) PKV_LB(G_, P_, S_, false, true);     \
