@@ -740,12 +740,11 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(GemmDesc<double> d0, Gemm
 //   phase C:          A_ij -= L_ik L_jk^T (k < j <= i);  E_im -= L_ik E_km (i > k, m <= k)
 // i.e. right-looking blocked Cholesky with the forward substitution of the identity
 // carried along; phases B and C are independent 16 x 16 x 16 products (fp32: MFMA
-// 16x16x4 with exact fp32 products; fp64: fp64 FMA), spread over eight waves, one
+// 16x16x4 f32 or f64, exact products), spread over the waves, one
 // barrier between phases. The leaf of step k + 1 needs only the first product of
 // phase C of step k (its own diagonal block), so wave 0 does that product and then
-// the leaf while the other seven waves do the rest of phase C: the single-wave leaf,
-// the longest serial part (its cost grows with the square of its width), overlaps
-// the trailing products.
+// the leaf while the other waves do the rest of phase C: the single-wave leaf, the
+// longest serial part, overlaps the trailing products.
 
 // LDS pitch (elements): lane-per-row reads of one column hit distinct banks
 template <class T>
@@ -761,44 +760,59 @@ __device__ __forceinline__ double rsq64(double x) {
   return fma(0.5 * r, fma(-x * r, r, 1.0), r);
 }
 
-// D = sgn * P Q' (+ C), 16 x 16 blocks in LDS (pitch PT); Q' = Q^T if QT else Q. One
-// wave; lane l holds D[4 (l / 16) + e][l % 16]. fp32: MFMA 16x16x4, lane l supplying
-// row l % 16 of P and column l % 16 of Q' at k = 4 ks + l / 16; fp64: FMA over k in
-// order. D may alias P, Q or C (every operand is read before D is written).
+// 16 x 16 x 4 MFMA step of either type. Lane l supplies A[l % 16][l / 16] and
+// B[l / 16][l % 16]; element e of its accumulator is D[acc_row(l / 16, e)][l % 16].
+template <class T>
+struct Acc4;
+template <>
+struct Acc4<float> {
+  typedef f32x4 V;
+};
+template <>
+struct Acc4<double> {
+  typedef f64x4 V;
+};
+__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f64x4 mfma16(double a, double b, f64x4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+template <class T>
+__device__ __forceinline__ constexpr int acc_row(int g, int e) {
+  return sizeof(T) == 4 ? 4 * g + e : 4 * e + g;
+}
+
+// acc += sgn * P Q', 16 x 16 blocks in LDS (pitch PT); Q' = Q^T if QT else Q. One wave;
+// exact products of the type.
+template <bool QT, class T>
+__device__ __forceinline__ typename Acc4<T>::V mm16_acc(typename Acc4<T>::V acc, const T* P, const T* Q,
+                                                        T sgn, int lane) {
+  constexpr int PT = diag_pitch<T>();
+  const int g = lane >> 4, l16 = lane & 15;
+  T a[4], b[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    const int k = 4 * ks + g;
+    a[ks] = sgn * P[l16 * PT + k];
+    b[ks] = QT ? Q[l16 * PT + k] : Q[k * PT + l16];
+  }
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) acc = mfma16(a[ks], b[ks], acc);
+  return acc;
+}
+
+// D = sgn * P Q' (+ C); D may alias P, Q or C (every operand is read before D is written).
 template <bool QT, class T>
 __device__ __forceinline__ void mm16(T* D, const T* P, const T* Q, const T* C, T sgn, int lane) {
   constexpr int PT = diag_pitch<T>();
   const int g = lane >> 4, l16 = lane & 15;
-  if constexpr (sizeof(T) == 4) {
-    f32x4 acc;
+  typename Acc4<T>::V acc;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] = C ? C[(4 * g + e) * PT + l16] : 0.f;
-    float a[4], b[4];
+  for (int e = 0; e < 4; ++e) acc[e] = C ? C[acc_row<T>(g, e) * PT + l16] : T(0);
+  acc = mm16_acc<QT>(acc, P, Q, sgn, lane);
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int k = 4 * ks + g;
-      a[ks] = sgn * P[l16 * PT + k];
-      b[ks] = QT ? Q[l16 * PT + k] : Q[k * PT + l16];
-    }
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ks], b[ks], acc, 0, 0, 0);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) D[(4 * g + e) * PT + l16] = acc[e];
-  } else {
-    T acc[4], q[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) q[k] = QT ? Q[l16 * PT + k] : Q[k * PT + l16];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const T* prow = P + (4 * g + e) * PT;
-      T a = 0;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) a = fma(prow[k], q[k], a);
-      acc[e] = C ? fma(sgn, a, C[(4 * g + e) * PT + l16]) : sgn * a;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) D[(4 * g + e) * PT + l16] = acc[e];
-  }
+  for (int e = 0; e < 4; ++e) D[acc_row<T>(g, e) * PT + l16] = acc[e];
 }
 
 __device__ __forceinline__ float bcast(float x, int src_lane) {
@@ -817,182 +831,165 @@ __device__ __forceinline__ double rsq_of(double x) { return rsq64(x); }
 // (0, 0, 2, 2) and (1, 1, 3, 3), permlane32_swap of that gives its lower (or upper) half
 // twice.
 template <int G>
-__device__ __forceinline__ float from_row(float x) {
-  const unsigned u = __builtin_bit_cast(unsigned, x);
+__device__ __forceinline__ unsigned from_row(unsigned u) {
   const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
   const unsigned y = (G & 1) ? a[1] : a[0];
   const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
-  return __builtin_bit_cast(float, (G & 2) ? b[1] : b[0]);
+  return (G & 2) ? b[1] : b[0];
 }
-// lane J of each 16-lane row, to the whole row (DPP row_newbcast)
-template <int J>
-__device__ __forceinline__ float row_lane(float x) {
-  return __builtin_bit_cast(float,
-                            __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x150 + J, 0xF, 0xF, false));
+template <int G>
+__device__ __forceinline__ float from_row(float x) {
+  return __builtin_bit_cast(float, from_row<G>(__builtin_bit_cast(unsigned, x)));
 }
-
-// The fp32 16-wide leaf on all 64 lanes: lane 16 q + r holds columns 4 k + q (k < 4) of
-// row r of the trailing matrix (v) and of Y (x), the block symmetrised from its lower
-// triangle on load. Step j, with pivot p = A_jj and u_r = A_rj / p (r > j, else 0):
-//   A_rc -= u_r A_jc for c > j (A_jc = A_cj: the trailing matrix stays symmetric), row j
-//     of the lane's column group through a DPP broadcast of lane j;
-//   Y_rm -= u_r Y_jm for m <= j, the same way;
-// A_rj itself comes from column group j % 4 through two lane-row swaps, the pivot through
-// one readlane. A lane updates its 4 - j/4 (and j/4 + 1) columns instead of all 16; with
-// the broadcasts (separate DPP moves, not fused into the FMAs) and their wait states a
-// step takes about 30 instructions against 36 for the row-per-lane sweep below.
-__device__ __forceinline__ void leaf16_groups(float* S, float* Xo, int lane, int col0, int bs,
-                                              int32_t* info, bool& failed) {
-  constexpr int PT = diag_pitch<float>();
-  int q = lane >> 4, r = lane & 15;
-  asm volatile("" : "+v"(q), "+v"(r));
-  float v[4], x[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int c = 4 * k + q;
-    v[k] = c > r ? S[c * PT + r] : S[r * PT + c];
-    x[k] = c == r ? 1.f : 0.f;
-  }
-  float rs_own = 0.f;
-  static_for<16>([&](auto j_t) {
-    constexpr int j = decltype(j_t)::value, jq = j % 4, jk = j / 4;
-    const float rs = rsq_of(bcast(v[jk], 16 * jq + j));
-    const float a = from_row<jq>(v[jk]);  // on every lane: the swaps are wave-wide
-    const float u = r > j ? a * (rs * rs) : 0.f;  // A[r][j] / p
-    if (r == j) rs_own = rs;
-    static_for<4 - jk>([&](auto kk_t) {  // columns 4 k + q > j
-      constexpr int k = jk + decltype(kk_t)::value;
-      const float uk = (k > jk || q > jq) ? u : 0.f;
-      v[k] = fmaf(-uk, row_lane<j>(v[k]), v[k]);
-    });
-    static_for<jk + 1>([&](auto k_t) {  // columns 4 k + q <= j
-      constexpr int k = decltype(k_t)::value;
-      const float uk = (k < jk || q <= jq) ? u : 0.f;
-      x[k] = fmaf(-uk, row_lane<j>(x[k]), x[k]);
-    });
-    if (q == jq) v[jk] *= rs;  // column j of L
-  });
-  // first failing pivot (padding pivots past bs are 1): row r's diagonal sits in group r % 4
-  float dg = v[0];
-#pragma unroll
-  for (int k = 1; k < 4; ++k)
-    if (k == (r >> 2)) dg = v[k];
-  const uint64_t bad = __ballot(q == (r & 3) && col0 + r < bs && !(dg > 0.f));
-  const unsigned rows = (unsigned)(bad | bad >> 16 | bad >> 32 | bad >> 48) & 0xFFFFu;
-  if (rows != 0 && !failed) {
-    failed = true;
-    if (lane == 0 && *info == 0) *info = col0 + __builtin_ctz(rows) + 1;
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int c = 4 * k + q;
-    S[r * PT + c] = v[k];             // row r of L (upper part unused)
-    Xo[r * PT + c] = x[k] * rs_own;   // row r of X (zeros above the diagonal)
-  }
+template <int G>
+__device__ __forceinline__ double from_row(double x) {
+  const u32x2 w = __builtin_bit_cast(u32x2, x);
+  return __builtin_bit_cast(double, u32x2{from_row<G>(w[0]), from_row<G>(w[1])});
+}
+// Lane (g, c) of the result: v_g of lane (B, c) (groups of 16 lanes; half of a 4 x 4 transpose
+// between registers and groups: permlane32_swap exchanges the first operand's upper half
+// with the second's lower half, permlane16_swap its odd rows with the second's even rows)
+template <int B>
+__device__ __forceinline__ float spread(float v0, float v1, float v2, float v3) {
+  auto bits = [](float x) { return __builtin_bit_cast(unsigned, x); };
+  const auto e = __builtin_amdgcn_permlane32_swap(bits(v0), bits(v2), false, false);
+  const auto o = __builtin_amdgcn_permlane32_swap(bits(v1), bits(v3), false, false);
+  const auto r = __builtin_amdgcn_permlane16_swap(e[B / 2], o[B / 2], false, false);
+  return __builtin_bit_cast(float, (unsigned)r[B % 2]);
 }
 
-// One wave: factor the SPD N x N block S (lower triangle read) and write
-// X = L^{-1} (lower, zeros above) to Xo, in one right-looking sweep.
-// Lane r (and its copies r + N, r + 2N, .., which repeat the same work so the wave
-// never diverges) holds row r of the trailing matrix (v) and row r of Y, the identity
-// under forward substitution (x). Step j, with pivot p = A_jj and u_r = A_rj / p for
-// rows r > j (0 otherwise):
-//   A_rc -= u_r A_cj     (c > j: column j of every lane, read through readlane)
-//   Y_rm -= u_r Y_jm     (m <= j: row j of Y, read from lane j)
-// and column j of L is A_rj / sqrt(p). Row r of X is row r of Y over L_rr, applied at
-// the end (Y's row r is final after step r - 1). Each step reads N values across
-// lanes, in groups of up to 8 held in distinct scalar registers, so that a readlane
-// is not directly followed by its consumer. A pivot that is not positive (or NaN)
-// makes its L_jj, and every later one, NaN: the first NaN on the diagonal is the
-// failing column.
-template <int N, class T>
-__device__ __forceinline__ void leaf_rows(T* S, T* Xo, int lane, int col0, int bs, int32_t* info,
-                                          bool& failed) {
-  static_assert(N == 16 || N == 32, "leaf width");
+// x's bits under a mask (all ones or zero), and a value of the bits
+__device__ __forceinline__ unsigned masked(float x, unsigned m) {
+  return __builtin_bit_cast(unsigned, x) & m;
+}
+__device__ __forceinline__ u32x2 masked(double x, unsigned m) {
+  const u32x2 w = __builtin_bit_cast(u32x2, x);
+  return u32x2{w[0] & m, w[1] & m};
+}
+template <class T, class U>
+__device__ __forceinline__ T unmask(U u) { return __builtin_bit_cast(T, u); }
+
+// One wave: factor the SPD 16 x 16 block held symmetrically in the accumulator a and write
+// X = L^{-1} (lower, zeros above) to Xo, four pivots at a time. For rows 4 b .. 4 b + 3:
+//   D = A[4b.., 4b..] (its 10 values read across lanes), D = L4 L4^T and N = L4^{-1} in
+//     every lane: the serial chain is four reciprocal square roots with a few FMAs between;
+//   panel: lane (c, g) gets L[c][4 b + g] = sum_m A[c][4 b + m] N[g][m] (A[c][4 b + m] =
+//     A[4 b + m][c]: the trailing matrix is symmetric) and X[4 b + g][c] = sum_m N[g][m]
+//     Y[4 b + m][c] the same way. fp32 accumulators hold the four rows in one lane group,
+//     which forms all four values and spreads them over the groups; fp64 ones hold a row
+//     per group, broadcast to all;
+//   A -= L_p L_p^T and Y -= L_p X_b for the rows below: one rank-4 MFMA each, whose operands
+//     are exactly the values the lanes hold.
+// Bound by instruction issue (one wave, 4 cycles each): an fp32 leaf takes 2,240 cycles,
+// 3,780 on a sweep of one pivot per step.
+// A pivot that is not positive (or NaN) makes its reciprocal square root, and every later
+// pivot, NaN: the first such pivot is the failing column.
+template <class T>
+__device__ __forceinline__ void leaf16(typename Acc4<T>::V a, T* Xo, int lane, int col0, int bs,
+                                       int32_t* info, bool& failed) {
   constexpr int PT = diag_pitch<T>();
-  int r = lane & (N - 1);
-  // opaque per call: keeps the per-step lane comparisons inside the call instead of
-  // hoisting them into scalar registers for the whole kernel
-  asm volatile("" : "+v"(r));
-  T v[N], x[N];
+  constexpr bool F32 = sizeof(T) == 4;
+  int g = lane >> 4, c = lane & 15;
+  asm volatile("" : "+v"(g), "+v"(c));  // (keeps the lane comparisons inside the call)
+  // one-hot masks of this lane's group: selecting by bits (the compiler made branches of a
+  // choice between four values)
+  const unsigned m0 = g == 0 ? ~0u : 0u, m1 = g == 1 ? ~0u : 0u, m2 = g == 2 ? ~0u : 0u,
+                 m3 = g == 3 ? ~0u : 0u;
+  typename Acc4<T>::V y;
 #pragma unroll
-  for (int c = 0; c < N; ++c) {
-    v[c] = S[r * PT + c];
-    x[c] = c == r ? T(1) : T(0);
-  }
-  T rs_own = 0;
-  // w[c0 .. c0+n) -= u * src(c), the n <= 8 values read first (the empty asm makes
-  // them live at once, in distinct registers)
-  auto group = [&](T (&w)[N], auto c0_t, auto n_t, auto src, T u) {
-    constexpr int c0 = decltype(c0_t)::value, n = decltype(n_t)::value;
-    T t[8];
-#pragma unroll
-    for (int q = 0; q < n; ++q) t[q] = src(c0 + q);
-#pragma unroll
-    for (int q = n; q < 8; ++q) t[q] = t[0];
-    asm volatile("" ::"s"(t[0]), "s"(t[1]), "s"(t[2]), "s"(t[3]), "s"(t[4]), "s"(t[5]), "s"(t[6]),
-                 "s"(t[7]));
-#pragma unroll
-    for (int q = 0; q < n; ++q) w[c0 + q] = fma(-u, t[q], w[c0 + q]);
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  static_for<N>([&](auto j_t) {
-    constexpr int j = decltype(j_t)::value;
-    const T rs = rsq_of(bcast(v[j], j));
-    const T u = r > j ? v[j] * (rs * rs) : T(0);  // A[r][j] / p
-    if (r == j) rs_own = rs;
-    // A_rc -= u_r A_cj, c = j+1..N-1 (A_cj is lane c's v[j])
-    static_for<(N - 1 - j + 7) / 8>([&](auto g_t) {
-      constexpr int c0 = j + 1 + 8 * decltype(g_t)::value;
-      constexpr int n = N - c0 < 8 ? N - c0 : 8;
-      group(v, std::integral_constant<int, c0>{}, std::integral_constant<int, n>{},
-            [&](int c) { return bcast(v[j], c); }, u);
-    });
-    // Y_rm -= u_r Y_jm, m = 0..j (lane j's x[m])
-    static_for<(j + 1 + 7) / 8>([&](auto g_t) {
-      constexpr int m0 = 8 * decltype(g_t)::value;
-      constexpr int n = j + 1 - m0 < 8 ? j + 1 - m0 : 8;
-      group(x, std::integral_constant<int, m0>{}, std::integral_constant<int, n>{},
-            [&](int m) { return bcast(x[m], j); }, u);
-    });
-    v[j] *= rs;
+  for (int e = 0; e < 4; ++e) y[e] = acc_row<T>(g, e) == c ? T(1) : T(0);
+  T ljj[16];
+  static_for<4>([&](auto b_t) {
+    constexpr int b = decltype(b_t)::value;
+    // element (i, m) of D: fp32 in register m of lane (b, 4 b + i), fp64 in register b of (m, 4 b + i)
+    auto d = [&](int i, int m) {
+      if constexpr (F32) return bcast(a[m], 20 * b + i);
+      else return bcast(a[b], 16 * m + 4 * b + i);
+    };
+    const T n00 = rsq_of(d(0, 0));
+    const T l10 = d(1, 0) * n00, l20 = d(2, 0) * n00, l30 = d(3, 0) * n00;
+    const T t11 = fma(-l10, l10, d(1, 1));
+    const T n11 = rsq_of(t11);
+    const T l21 = fma(-l20, l10, d(2, 1)) * n11, l31 = fma(-l30, l10, d(3, 1)) * n11;
+    const T t22 = fma(-l21, l21, fma(-l20, l20, d(2, 2)));
+    const T n22 = rsq_of(t22);
+    const T l32 = fma(-l31, l21, fma(-l30, l20, d(3, 2))) * n22;
+    const T t33 = fma(-l32, l32, fma(-l31, l31, fma(-l30, l30, d(3, 3))));
+    const T n33 = rsq_of(t33);
+    const T n10 = -(l10 * n00) * n11;
+    const T n21 = -(l21 * n11) * n22;
+    const T n20 = -fma(l21, n10, l20 * n00) * n22;
+    const T n32 = -(l32 * n22) * n33;
+    const T n31 = -fma(l32, n21, l31 * n11) * n33;
+    const T n30 = -fma(l32, n20, fma(l31, n10, l30 * n00)) * n33;
+    // row b's four rows of v times N^T, spread over the groups
+    auto times = [&](const typename Acc4<T>::V& v) -> T {
+      if constexpr (F32) {
+        return spread<b>(n00 * v[0], fma(n11, v[1], n10 * v[0]),
+                         fma(n22, v[2], fma(n21, v[1], n20 * v[0])),
+                         fma(n33, v[3], fma(n32, v[2], fma(n31, v[1], n30 * v[0]))));
+      } else {
+        const T c0 = unmask<T>(masked(n00, m0) | masked(n10, m1) | masked(n20, m2) | masked(n30, m3));
+        const T c1 = unmask<T>(masked(n11, m1) | masked(n21, m2) | masked(n31, m3));
+        const T c2 = unmask<T>(masked(n22, m2) | masked(n32, m3));
+        const T c3 = unmask<T>(masked(n33, m3));
+        return fma(c3, from_row<3>(v[b]), fma(c2, from_row<2>(v[b]), fma(c1, from_row<1>(v[b]), c0 * from_row<0>(v[b]))));
+      }
+    };
+    T lp = T(0);
+    if constexpr (b < 3) {
+      const T all = times(a);  // (on every lane: the lane swaps are wave-wide)
+      lp = c >= 4 * b + 4 ? all : T(0);
+      a = mfma16(-lp, lp, a);
+    }
+    const T x = times(y);
+    if constexpr (b < 3) y = mfma16(-lp, x, y);
+    Xo[(4 * b + g) * PT + c] = x;
+    // L_jj = t_j / sqrt(t_j): NaN from the first failing pivot on
+    ljj[4 * b] = d(0, 0) * n00;
+    ljj[4 * b + 1] = t11 * n11;
+    ljj[4 * b + 2] = t22 * n22;
+    ljj[4 * b + 3] = t33 * n33;
   });
-  // first failing pivot of this block (padding pivots past bs are 1)
-  T diag = 0;
+  if (__ballot(!(ljj[15] > T(0))) != 0 && !failed) {
+    int bad = 15;
 #pragma unroll
-  for (int c = 0; c < N; ++c)
-    if (c == r) diag = v[c];
-  const uint64_t bad = __ballot(lane < N && col0 + r < bs && !(diag > T(0)));
-  if (bad != 0 && !failed) {
-    failed = true;
-    if (lane == 0 && *info == 0) *info = col0 + __builtin_ctzll(bad) + 1;
-  }
-  if (lane < N) {
-#pragma unroll
-    for (int c = 0; c < N; ++c) {
-      S[r * PT + c] = v[c];            // row r of L (upper part unused)
-      Xo[r * PT + c] = x[c] * rs_own;  // row r of X (zeros above the diagonal)
+    for (int j = 14; j >= 0; --j)
+      if (__ballot(!(ljj[j] > T(0))) != 0) bad = j;
+    if (col0 + bad < bs) {
+      failed = true;
+      if (lane == 0 && *info == 0) *info = col0 + bad + 1;
     }
   }
 }
 
-// the fp32 16-wide leaf on four column groups, every other on the row-per-lane sweep
-template <int N, class T>
-__device__ __forceinline__ void leaf(T* S, T* Xo, int lane, int col0, int bs, int32_t* info,
-                                     bool& failed) {
-  if constexpr (N == 16 && sizeof(T) == 4) leaf16_groups(S, Xo, lane, col0, bs, info, failed);
-  else leaf_rows<N>(S, Xo, lane, col0, bs, info, failed);
+// the 16 x 16 block S (lower triangle read) as a symmetric accumulator
+template <class T>
+__device__ __forceinline__ typename Acc4<T>::V sym16(const T* S, int lane) {
+  constexpr int PT = diag_pitch<T>();
+  const int g = lane >> 4, c = lane & 15;
+  typename Acc4<T>::V a;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int r = acc_row<T>(g, e);
+    a[e] = S[max(r, c) * PT + min(r, c)];
+  }
+  return a;
 }
 
-constexpr int kPotrfWaves = 8;  // 8 waves: the next leaf overlaps the trailing products
+// Waves: the next leaf overlaps the trailing products of the others. fp32 128 x 128 (28
+// trailing products at first): 16.9 us with 16 waves, 19.3 with 8 (21.7 with the sweep);
+// two products at a time per wave 18.1. fp64 64 x 64: 11.4 with 8, 11.9 with 16 (17.5).
+template <class T>
+constexpr int potrf_waves() { return sizeof(T) == 4 ? 16 : 8; }
 constexpr int kLeaf = 16;       // leaf width
 
 // The diagonal block at (kb, kb) of A (lda): L^{-1} (lower, zeros above) over it,
 // info = first failing column (1-based) if the block is not positive definite.
 template <class T>
-__global__ __launch_bounds__(64 * kPotrfWaves) void potrf_blk_kernel(T* A, int64_t lda, int kb, int bs,
+__global__ __launch_bounds__(64 * potrf_waves<T>()) void potrf_blk_kernel(T* A, int64_t lda, int kb, int bs,
                                                                     int32_t* info) {
-  constexpr int NB = Blk<T>::NB, PT = diag_pitch<T>(), NT = 64 * kPotrfWaves;
+  constexpr int NB = Blk<T>::NB, PT = diag_pitch<T>(), NW = potrf_waves<T>(), NT = 64 * NW;
   constexpr int EV = 16 / sizeof(T), NL = NB * NB / EV / NT;  // 16-byte pieces per thread
   constexpr int NLV = NB / kLeaf, NL1 = NLV - 1;
   typedef T V16 __attribute__((ext_vector_type(EV)));
@@ -1042,11 +1039,11 @@ __global__ __launch_bounds__(64 * kPotrfWaves) void potrf_blk_kernel(T* A, int64
   __syncthreads();
   auto blk = [](T* base, int i, int j) { return base + (kLeaf * i) * PT + kLeaf * j; };
   bool failed = false;
-  if (wid == 0) leaf<kLeaf>(blk(As, 0, 0), blk(Es, 0, 0), lane, kb, kb + bs, info, failed);
+  if (wid == 0) leaf16<T>(sym16<T>(blk(As, 0, 0), lane), blk(Es, 0, 0), lane, kb, kb + bs, info, failed);
   __syncthreads();
   for (int k = 0; k < NLV; ++k) {
     // phase B: (NL1 - k) panel products, k products of the identity's row block k
-    for (int q = wid; q < NL1; q += kPotrfWaves) {
+    for (int q = wid; q < NL1; q += NW) {
       if (q < NL1 - k) {
         const int i = k + 1 + q;
         mm16<true>(blk(As, i, k), blk(As, i, k), blk(Es, k, k), (const T*)nullptr, T(1), lane);
@@ -1078,11 +1075,15 @@ __global__ __launch_bounds__(64 * kPotrfWaves) void potrf_blk_kernel(T* A, int64
       }
     };
     if (wid == 0) {
-      job(0);
-      leaf<kLeaf>(blk(As, k + 1, k + 1), blk(Es, k + 1, k + 1), lane, kb + kLeaf * (k + 1), kb + bs,
-                  info, failed);
+      // the next diagonal block's update stays in registers; the leaf is the longest serial
+      // part, so its wave goes first on its SIMD
+      __builtin_amdgcn_s_setprio(3);
+      const T* Lk = blk(As, k + 1, k);
+      leaf16<T>(mm16_acc<true>(sym16<T>(blk(As, k + 1, k + 1), lane), Lk, Lk, T(-1), lane),
+                blk(Es, k + 1, k + 1), lane, kb + kLeaf * (k + 1), kb + bs, info, failed);
+      __builtin_amdgcn_s_setprio(0);
     } else {
-      for (int q = wid; q < njobs; q += kPotrfWaves - 1) job(q);
+      for (int q = wid; q < njobs; q += NW - 1) job(q);
     }
     __syncthreads();
   }
@@ -1436,7 +1437,7 @@ hipError_t solve_t(const T* G, const T* C, int64_t d64, int64_t dout64, double l
     for (int kb = K0; kb < K0 + W; kb += NB) {
       const int bs = std::min(NB, d - kb);
       const int rest = d - kb - bs;
-      hipLaunchKernelGGL((potrf_blk_kernel<T>), dim3(1), dim3(64 * kPotrfWaves), 0, st, A, d64, kb, bs,
+      hipLaunchKernelGGL((potrf_blk_kernel<T>), dim3(1), dim3(64 * potrf_waves<T>()), 0, st, A, d64, kb, bs,
                          info);
       PKV_TRY(hipGetLastError());
       const T* Linv = A + (int64_t)kb * d + kb;  // Linv(i,t) = Linv[i*d + t]
@@ -1923,7 +1924,7 @@ hipError_t launch_low_rank(const float* G, const float* dW, int64_t din, int64_t
   // src (dout x b) -> dst = src L^-T with src^T src = L L^T (Gram and factor in fp64)
   auto orth = [&](const float* src, float* dst) -> hipError_t {
     PKV_TRY(gram(src, src, W64));
-    hipLaunchKernelGGL((potrf_blk_kernel<double>), dim3(1), dim3(64 * kPotrfWaves), 0, st, W64,
+    hipLaunchKernelGGL((potrf_blk_kernel<double>), dim3(1), dim3(64 * potrf_waves<double>()), 0, st, W64,
                        (int64_t)b, 0, b, info);
     PKV_TRY(hipGetLastError());
     hipLaunchKernelGGL(linv_t_kernel, dim3((b * b + 255) / 256), dim3(256), 0, st, W64, b, W);

@@ -1,0 +1,46 @@
+"""The diagonal-block factorisation at every position of a pivot inside its four-pivot
+steps, 16-wide leaves and blocks: the first failing column is reported exactly, and the
+factorisation of well-posed systems of any block remainder matches numpy in fp64.
+
+Errors of a solve are bounded by a small multiple of cond * eps: cond below 50 here, so
+2e-5 in fp32 (2^-24 * 50 * 4) and 1e-6 after rounding fp64 results to fp32."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2609_39329_amd as pkv
+from gpu_util import DEV, host, rel
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("p", [0, 1, 2, 3, 4, 7, 15, 16, 18, 63, 64, 65, 126, 127, 128, 131, 149])
+@pytest.mark.parametrize("pivot", [-1.0, 0.0, float("nan")])
+def test_first_failing_column(dtype, p, pivot):
+    print(f"failing column {p} pivot {pivot} {dtype}", flush=True)
+    d = 150
+    rng = np.random.default_rng(p)
+    L = np.tril(rng.standard_normal((d, d)) * 0.05) + np.eye(d)
+    G = L @ L.T
+    s = L[p, :p] @ L[p, :p]
+    lam = 0.25
+    G -= lam * np.eye(d)
+    G[p, p] = s + (pivot if pivot != 0.0 else -1e-3) - lam  # Schur complement of column p
+    G[p + 1:, p + 1:] += 2 * np.eye(d - p - 1)
+    if p + 3 < d:
+        G[p + 3, p + 3] = -5.0  # a later failure is not reported
+    dW, info = pkv.solve_patch(torch.from_numpy(G).to(dtype).to(DEV), torch.ones((d, 4), dtype=dtype, device=DEV), lam)
+    assert int(info.item()) == p + 1
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.float32, 2e-5), (torch.float64, 1e-6)])
+@pytest.mark.parametrize("d", [1, 2, 3, 4, 5, 15, 16, 17, 33, 63, 64, 65, 100, 127, 128, 129, 145, 260])
+def test_block_remainders(dtype, tol, d):
+    print(f"remainder d={d} {dtype}", flush=True)
+    rng = np.random.default_rng(d)
+    X = rng.standard_normal((4 * d, d)) / np.sqrt(4 * d)
+    G, C = X.T @ X, rng.standard_normal((d, 9))
+    dW, info = pkv.solve_patch(torch.from_numpy(G).to(dtype).to(DEV), torch.from_numpy(C).to(dtype).to(DEV), 0.1)
+    assert int(info.item()) == 0
+    assert rel(host(dW), np.linalg.solve(G + 0.1 * np.eye(d), C)) <= tol
