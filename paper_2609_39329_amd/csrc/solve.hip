@@ -301,35 +301,53 @@ struct SLayout {
 // CHECK: bounds-checked staging loads (edge tiles); without it the tile must lie
 // inside M x N, K must be a multiple of the chunk and both operands vector-aligned,
 // and the loads are plain 16-byte loads from pointers advanced once per chunk.
-template <int TERMS, bool AK, bool BJ, bool CHECK>
+template <int TERMS, bool AK, bool BJ, bool CHECK, int KSP>
 __device__ __forceinline__ void sgemm3_tile(const SGemm& g, int i0, int j0, __bf16* lds);
 
-// tile t of g (lower: the triangle's tiles in row order)
-template <int TERMS, bool AK, bool BJ>
-__device__ __forceinline__ void sgemm3_body(const SGemm& g, int t, __bf16* lds) {
-  int ti, tj;
-  if (g.lower) {
+// tile t of g (lower: the tiles with tile_row >= tile_col in row order, a triangle and then
+// whole rows)
+__device__ __forceinline__ void tile_of(const SGemm& g, int t, int& ti, int& tj) {
+  const int tri = g.lower ? g.tiles_n * (g.tiles_n + 1) / 2 : 0;
+  if (t < tri) {
     ti = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
     while ((ti + 1) * (ti + 2) / 2 <= t) ++ti;
     while (ti * (ti + 1) / 2 > t) --ti;
     tj = t - ti * (ti + 1) / 2;
   } else {
-    ti = t / g.tiles_n;
-    tj = t % g.tiles_n;
+    const int r = t - tri;
+    ti = (g.lower ? g.tiles_n : 0) + r / g.tiles_n;
+    tj = r % g.tiles_n;
   }
+}
+
+template <int TERMS, bool AK, bool BJ, int KSP>
+__device__ __forceinline__ void sgemm3_body(SGemm g, int t, __bf16* lds) {
+  int ti, tj;
+  tile_of(g, t, ti, tj);
   const int i0 = ti * S_BM, j0 = tj * S_BM;
   const bool interior = i0 + S_BM <= g.M && j0 + S_BM <= g.N && g.K % SLayout<TERMS>::KC == 0 &&
                         g.vecA && g.vecB;
-  if (interior) sgemm3_tile<TERMS, AK, BJ, false>(g, i0, j0, lds);
-  else sgemm3_tile<TERMS, AK, BJ, true>(g, i0, j0, lds);
+  if constexpr (KSP == 2) {
+    // this half of the workgroup's half of K (K a multiple of 2 chunks), in its own buffers
+    const int h = threadIdx.x >> 8;
+    g.K /= 2;
+    g.A += (int64_t)h * g.K * (AK ? 1 : g.sa);
+    g.B += (int64_t)h * g.K * (BJ ? g.sb : 1);
+    lds += h * SLayout<TERMS>::LDS;
+  }
+  if (interior) sgemm3_tile<TERMS, AK, BJ, false, KSP>(g, i0, j0, lds);
+  else sgemm3_tile<TERMS, AK, BJ, true, KSP>(g, i0, j0, lds);
 }
 
-template <int TERMS, bool AK, bool BJ, bool CHECK>
+// KSP = 2: called by both halves of a 512-thread workgroup, each with half of K; the
+// second half's sums go through its buffers to the first, which stores the tile.
+template <int TERMS, bool AK, bool BJ, bool CHECK, int KSP>
 __device__ __forceinline__ void sgemm3_tile(const SGemm& g, int i0, int j0, __bf16* lds) {
   using LY = SLayout<TERMS>;
   constexpr int KC = LY::KC, NP = Split<TERMS>::P;
   constexpr int NU = S_BM * KC / 4 / 256;  // float4 runs per thread, operand and chunk
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int half = KSP == 2 ? threadIdx.x >> 8 : 0;
+  const int tid = threadIdx.x & 255, lane = tid & 63, wid = tid >> 6;
   const int h32 = lane >> 5, l32 = lane & 31;
   const int wi = (wid >> 1) * 64, wj = (wid & 1) * 64;
   // [row][k] when the contraction index is contiguous in memory, else [k][row]
@@ -338,7 +356,7 @@ __device__ __forceinline__ void sgemm3_tile(const SGemm& g, int i0, int j0, __bf
 
   // C tile prefetch: lane owns C[i0+wi+32a+l32][j0+wj+32b+8q+4h32 .. +3]
   f32x4 cpre[2][2][4];
-  const bool use_c = g.beta != 0.f;
+  const bool use_c = g.beta != 0.f && half == 0;
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -478,6 +496,18 @@ __device__ __forceinline__ void sgemm3_tile(const SGemm& g, int i0, int j0, __bf
     __syncthreads();
   }
 
+  if constexpr (KSP == 2) {
+    static_assert(LY::LDS * 2 >= 64 * 256 * 4, "the partial sums fit one half's buffers");
+    float* part = (float*)(half ? lds : lds + LY::LDS);
+    if (half) {
+#pragma unroll
+      for (int e = 0; e < 64; ++e) part[e * 256 + tid] = acc[e >> 5][(e >> 4) & 1][e & 15];
+    }
+    __syncthreads();
+    if (half) return;
+#pragma unroll
+    for (int e = 0; e < 64; ++e) acc[e >> 5][(e >> 4) & 1][e & 15] += part[e * 256 + tid];
+  }
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -500,54 +530,56 @@ __device__ __forceinline__ void sgemm3_tile(const SGemm& g, int i0, int j0, __bf
 
 // Up to two problems per launch, each with its own operand layout; work items are
 // spread so that consecutive tiles of one problem share an XCD (and its L2).
-template <int TERMS, bool AK0, bool BJ0, bool AK1, bool BJ1>
-__global__ __launch_bounds__(256, 2) void sgemm3_kernel(SGemm d0, SGemm d1) {
-  __shared__ __attribute__((aligned(16))) __bf16 lds[SLayout<TERMS>::LDS];
+// KSP = 2 (launches of at most one tile per CU): a second set of four waves takes half of K, so
+// each SIMD has two waves to hide latency with: a 1024 x 4096 product over K = 1024 (256
+// tiles) 53 us, about 60 without.
+template <int TERMS, bool AK0, bool BJ0, bool AK1, bool BJ1, int KSP>
+__global__ __launch_bounds__(256 * KSP, 3 - KSP) void sgemm3_kernel(SGemm d0, SGemm d1) {
+  __shared__ __attribute__((aligned(16))) __bf16 lds[KSP * SLayout<TERMS>::LDS];
   const int total = d0.ntiles + d1.ntiles;
   const int t = xcd_item((total + kXcds - 1) / kXcds);
   if (t >= total) return;
   if (t < d0.ntiles) {
     int u = t;
     const SGemm g = batch_item(d0, u);
-    sgemm3_body<TERMS, AK0, BJ0>(g, u, lds);
+    sgemm3_body<TERMS, AK0, BJ0, KSP>(g, u, lds);
   } else {
     int u = t - d0.ntiles;
     const SGemm g = batch_item(d1, u);
-    sgemm3_body<TERMS, AK1, BJ1>(g, u, lds);
+    sgemm3_body<TERMS, AK1, BJ1, KSP>(g, u, lds);
   }
 }
 
-// ---- the same split products for K <= 128: 64 x 64 tiles, one staging round ----------
+// ---- the same split products for K <= 128: 64 x 64 tiles ------------------------------
 //
 // The small updates of the factorisation (K = one block column) are latency bound:
 // with 128 x 128 tiles a launch has few workgroups and every chunk waits for its loads.
-// Here each workgroup (4 waves of 32 x 32) loads its whole K range in one round (K
-// padded to 16 with zeros, bounds-checked), splits it into bf16 planes in LDS and runs
-// the MFMAs with no further waits.
+// Here each workgroup (4 waves of 32 x 32) stages KS of its K range at a time (K
+// padded to 16 with zeros, bounds-checked), split into bf16 planes in LDS:
+//   KS = 128, for launches of one round (<= 256 tiles): one round of loads, no further
+//     waits, one workgroup per CU (six-term planes take 120 KB of LDS): 8 us;
+//   KS = 64, for more tiles: 60 KB, so two workgroups of a CU overlap their loads, splits
+//     and products: 512 tiles 11.3 us (13.9 with KS = 128), 900 tiles 20 (25).
 constexpr int T_BM = 64, T_KMAX = 128;
-constexpr int T_PK = T_KMAX + 8;  // pitch of a [row][k] LDS tile (bf16)
-constexpr int T_PR = T_BM + 16;   // pitch of a [k][row] LDS tile (bf16)
-constexpr int T_TILE = T_BM * T_PK > T_KMAX * T_PR ? T_BM * T_PK : T_KMAX * T_PR;  // bf16 per plane
+template <int KS>
+struct TLayout {
+  static constexpr int PK = KS + 8;    // pitch of a [row][k] LDS tile (bf16)
+  static constexpr int PR = T_BM + 16;   // pitch of a [k][row] LDS tile (bf16)
+  static constexpr int TILE = T_BM * PK > KS * PR ? T_BM * PK : KS * PR;  // bf16 per plane
+};
 
-template <int TERMS, bool AK, bool BJ>
+template <int TERMS, bool AK, bool BJ, int KS>
 __device__ __forceinline__ void sgemm3s_body(const SGemm& g, int t, __bf16* lds) {
+  using LY = TLayout<KS>;
   constexpr int NP = Split<TERMS>::P;
   int ti, tj;
-  if (g.lower) {
-    ti = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
-    while ((ti + 1) * (ti + 2) / 2 <= t) ++ti;
-    while (ti * (ti + 1) / 2 > t) --ti;
-    tj = t - ti * (ti + 1) / 2;
-  } else {
-    ti = t / g.tiles_n;
-    tj = t % g.tiles_n;
-  }
+  tile_of(g, t, ti, tj);
   const int i0 = ti * T_BM, j0 = tj * T_BM;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int h32 = lane >> 5, l32 = lane & 31;
   const int wi = (wid >> 1) * 32, wj = (wid & 1) * 32;
   constexpr bool a_rk = AK, b_rk = !BJ;
-  constexpr int PA = a_rk ? T_PK : T_PR, PB = b_rk ? T_PK : T_PR;
+  constexpr int PA = a_rk ? LY::PK : LY::PR, PB = b_rk ? LY::PK : LY::PR;
   const int Kp = (g.K + 15) & ~15;
 
   // C prefetch: lane owns C[i0+wi+l32][j0+wj+8q+4h32 .. +3]
@@ -567,65 +599,65 @@ __device__ __forceinline__ void sgemm3s_body(const SGemm& g, int t, __bf16* lds)
     cpre[q] = v;
   }
 
-  // the whole K range: 64 x Kp per operand = up to 8 runs of 4 floats per thread
-  constexpr int NU = T_BM * T_KMAX / 4 / 256;
+  // KS k of both operands: 64 x KS per operand, in runs of 4 floats
+  constexpr int NU = T_BM * KS / 4 / 256;
   f32x4 ra[NU], rb[NU];
+  auto fetch = [&](int k0) {
 #pragma unroll
-  for (int u = 0; u < NU; ++u) {
-    const int c = u * 256 + tid;
-    {
-      int i, k;
-      if constexpr (AK) { i = c / (T_KMAX / 4); k = (c % (T_KMAX / 4)) * 4; }
-      else { k = c / (T_BM / 4); i = (c % (T_BM / 4)) * 4; }
-      const int gi = i0 + i;
-      const int nvalid = AK ? (gi < g.M ? g.K - k : 0) : (k < g.K ? g.M - gi : 0);
-      const float* src = g.A + (AK ? (int64_t)gi * g.sa + k : (int64_t)k * g.sa + gi);
-      f32x4 v = {};
-      if (k < Kp) {
-        if (nvalid >= 4 && g.vecA) v = *(const f32x4*)src;
-        else
-          for (int e = 0; e < 4; ++e)
-            if (e < nvalid) v[e] = src[e];
+    for (int u = 0; u < NU; ++u) {
+      const int c = u * 256 + tid;
+      {
+        int i, k;
+        if constexpr (AK) { i = c / (KS / 4); k = k0 + (c % (KS / 4)) * 4; }
+        else { k = k0 + c / (T_BM / 4); i = (c % (T_BM / 4)) * 4; }
+        const int gi = i0 + i;
+        const int nvalid = AK ? (gi < g.M ? g.K - k : 0) : (k < g.K ? g.M - gi : 0);
+        const float* src = g.A + (AK ? (int64_t)gi * g.sa + k : (int64_t)k * g.sa + gi);
+        f32x4 v = {};
+        if (k < Kp) {
+          if (nvalid >= 4 && g.vecA) v = *(const f32x4*)src;
+          else
+            for (int e = 0; e < 4; ++e)
+              if (e < nvalid) v[e] = src[e];
+        }
+        ra[u] = v;
       }
-      ra[u] = v;
-    }
-    {
-      int j, k;
-      if constexpr (BJ) { k = c / (T_BM / 4); j = (c % (T_BM / 4)) * 4; }
-      else { j = c / (T_KMAX / 4); k = (c % (T_KMAX / 4)) * 4; }
-      const int gj = j0 + j;
-      const int nvalid = BJ ? (k < g.K ? g.N - gj : 0) : (gj < g.N ? g.K - k : 0);
-      const float* src = g.B + (BJ ? (int64_t)k * g.sb + gj : (int64_t)gj * g.sb + k);
-      f32x4 v = {};
-      if (k < Kp) {
-        if (nvalid >= 4 && g.vecB) v = *(const f32x4*)src;
-        else
-          for (int e = 0; e < 4; ++e)
-            if (e < nvalid) v[e] = src[e];
+      {
+        int j, k;
+        if constexpr (BJ) { k = k0 + c / (T_BM / 4); j = (c % (T_BM / 4)) * 4; }
+        else { j = c / (KS / 4); k = k0 + (c % (KS / 4)) * 4; }
+        const int gj = j0 + j;
+        const int nvalid = BJ ? (k < g.K ? g.N - gj : 0) : (gj < g.N ? g.K - k : 0);
+        const float* src = g.B + (BJ ? (int64_t)k * g.sb + gj : (int64_t)gj * g.sb + k);
+        f32x4 v = {};
+        if (k < Kp) {
+          if (nvalid >= 4 && g.vecB) v = *(const f32x4*)src;
+          else
+            for (int e = 0; e < 4; ++e)
+              if (e < nvalid) v[e] = src[e];
+        }
+        rb[u] = v;
       }
-      rb[u] = v;
     }
-  }
+  };
   __bf16* pa_[NP];
   __bf16* pb_[NP];
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
-    pa_[q] = lds + q * T_TILE;
-    pb_[q] = lds + (NP + q) * T_TILE;
+    pa_[q] = lds + q * LY::TILE;
+    pb_[q] = lds + (NP + q) * LY::TILE;
   }
+  // (planes past K hold zeros: fetch clears what it does not load)
+  auto stash = [&]() {
 #pragma unroll
-  for (int u = 0; u < NU; ++u) {
-    const int c = u * 256 + tid;
-    const int ka = AK ? (c % (T_KMAX / 4)) * 4 : c / (T_BM / 4);
-    const int kb = BJ ? c / (T_BM / 4) : (c % (T_KMAX / 4)) * 4;
-    if (ka < Kp)
-      split_store<NP>(pa_, a_rk ? (c / (T_KMAX / 4)) * PA + (c % (T_KMAX / 4)) * 4
+    for (int u = 0; u < NU; ++u) {
+      const int c = u * 256 + tid;
+      split_store<NP>(pa_, a_rk ? (c / (KS / 4)) * PA + (c % (KS / 4)) * 4
                                 : (c / (T_BM / 4)) * PA + (c % (T_BM / 4)) * 4, ra[u]);
-    if (kb < Kp)
-      split_store<NP>(pb_, b_rk ? (c / (T_KMAX / 4)) * PB + (c % (T_KMAX / 4)) * 4
+      split_store<NP>(pb_, b_rk ? (c / (KS / 4)) * PB + (c % (KS / 4)) * 4
                                 : (c / (T_BM / 4)) * PB + (c % (T_BM / 4)) * 4, rb[u]);
-  }
-  __syncthreads();
+    }
+  };
   // 32 rows x 8 k fragment (row r0 + l32, k k0 + 8 h32 ..) of an LDS tile
   const int tr_k = 8 * h32 + ((lane & 15) >> 2);
   const int tr_r = ((lane >> 4) & 1) * 16 + 4 * (lane & 3);
@@ -635,14 +667,22 @@ __device__ __forceinline__ void sgemm3s_body(const SGemm& g, int t, __bf16* lds)
     return cat8(lds_read_tr16(q), lds_read_tr16(q + 4 * pitch));
   };
   f32x16 acc = {};
-  for (int ks = 0; ks < Kp; ks += 16) {
-    bf16x8 fa[NP], fb[NP];
+  fetch(0);
+  for (int k0 = 0; k0 < Kp; k0 += KS) {
+    stash();
+    if (k0 + KS < Kp) fetch(k0 + KS);
+    __syncthreads();
+    const int kn = min(KS, Kp - k0);
+    for (int ks = 0; ks < kn; ks += 16) {
+      bf16x8 fa[NP], fb[NP];
 #pragma unroll
-    for (int q = 0; q < NP; ++q) {
-      fa[q] = frag(pa_[q], PA, a_rk, wi, ks);
-      fb[q] = frag(pb_[q], PB, b_rk, wj, ks);
+      for (int q = 0; q < NP; ++q) {
+        fa[q] = frag(pa_[q], PA, a_rk, wi, ks);
+        fb[q] = frag(pb_[q], PB, b_rk, wj, ks);
+      }
+      acc = split_mfma<TERMS>(fb, fa, acc);
     }
-    acc = split_mfma<TERMS>(fb, fa, acc);
+    if (k0 + KS < Kp) __syncthreads();
   }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -660,22 +700,20 @@ __device__ __forceinline__ void sgemm3s_body(const SGemm& g, int t, __bf16* lds)
   }
 }
 
-// (six-term planes take 120 KB of LDS: one workgroup per CU; these launches are few
-// workgroups anyway)
-template <int TERMS, bool AK0, bool BJ0, bool AK1, bool BJ1>
-__global__ __launch_bounds__(256, TERMS == 6 ? 1 : 2) void sgemm3s_kernel(SGemm d0, SGemm d1) {
-  __shared__ __attribute__((aligned(16))) __bf16 lds[2 * Split<TERMS>::P * T_TILE];
+template <int TERMS, bool AK0, bool BJ0, bool AK1, bool BJ1, int KS>
+__global__ __launch_bounds__(256, TERMS == 6 && KS == 128 ? 1 : 2) void sgemm3s_kernel(SGemm d0, SGemm d1) {
+  __shared__ __attribute__((aligned(16))) __bf16 lds[2 * Split<TERMS>::P * TLayout<KS>::TILE];
   const int total = d0.ntiles + d1.ntiles;
   const int t = xcd_item((total + kXcds - 1) / kXcds);
   if (t >= total) return;
   if (t < d0.ntiles) {
     int u = t;
     const SGemm g = batch_item(d0, u);
-    sgemm3s_body<TERMS, AK0, BJ0>(g, u, lds);
+    sgemm3s_body<TERMS, AK0, BJ0, KS>(g, u, lds);
   } else {
     int u = t - d0.ntiles;
     const SGemm g = batch_item(d1, u);
-    sgemm3s_body<TERMS, AK1, BJ1>(g, u, lds);
+    sgemm3s_body<TERMS, AK1, BJ1, KS>(g, u, lds);
   }
 }
 
@@ -986,9 +1024,13 @@ constexpr int kLeaf = 16;       // leaf width
 
 // The diagonal block at (kb, kb) of A (lda): L^{-1} (lower, zeros above) over it,
 // info = first failing column (1-based) if the block is not positive definite.
-template <class T>
+// SLICES > 0 (the reduced-rank patch's Cholesky QR; kb = 0, lda = bs): the block is the sum
+// over SLICES partial blocks, added in order, from A on, and L^{-T} goes to Wt [bs][bs] in
+// fp32: 16.1 us for 4 slices, 21.7 with a launch each for the sum and the transpose (with
+// 16 slices the one workgroup's 512 KB of loads took it to 32 us).
+template <class T, int SLICES>
 __global__ __launch_bounds__(64 * potrf_waves<T>()) void potrf_blk_kernel(T* A, int64_t lda, int kb, int bs,
-                                                                    int32_t* info) {
+                                                                    int32_t* info, float* Wt) {
   constexpr int NB = Blk<T>::NB, PT = diag_pitch<T>(), NW = potrf_waves<T>(), NT = 64 * NW;
   constexpr int EV = 16 / sizeof(T), NL = NB * NB / EV / NT;  // 16-byte pieces per thread
   constexpr int NLV = NB / kLeaf, NL1 = NLV - 1;
@@ -1014,6 +1056,18 @@ __global__ __launch_bounds__(64 * potrf_waves<T>()) void potrf_blk_kernel(T* A, 
 #pragma unroll
         for (int t = 0; t < EV; ++t)
           buf[u][t] = (i < bs && j0 + t < bs) ? src[t] : (i == j0 + t ? T(1) : T(0));
+      }
+    }
+    if constexpr (SLICES > 0) {
+      // (the partials of a slice together: bs is even, so a run lies inside or outside)
+#pragma unroll 4
+      for (int z = 1; z < SLICES; ++z) {
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+          const int e = (u * NT + tid) * EV;
+          const int i = e / NB, j0 = e % NB;
+          if (i < bs && j0 < bs) buf[u] += *(const V16*)(A + ((int64_t)z * bs + i) * bs + j0);
+        }
       }
     }
 #pragma unroll
@@ -1095,6 +1149,12 @@ __global__ __launch_bounds__(64 * potrf_waves<T>()) void potrf_blk_kernel(T* A, 
     const int e = (u * NT + tid2) * EV;
     const int i = e / NB, j0 = e % NB;
     if (i >= bs) continue;
+    if constexpr (SLICES > 0) {  // row i of L^{-T}
+#pragma unroll
+      for (int t = 0; t < EV; ++t)
+        if (j0 + t < bs) Wt[i * bs + j0 + t] = i <= j0 + t ? (float)Es[(j0 + t) * PT + i] : 0.f;
+      continue;
+    }
     V16 v;
 #pragma unroll
     for (int t = 0; t < EV; ++t) v[t] = j0 + t <= i ? Es[i * PT + j0 + t] : T(0);
@@ -1106,25 +1166,17 @@ __global__ __launch_bounds__(64 * potrf_waves<T>()) void potrf_blk_kernel(T* A, 
   }
 }
 
-// Zeros above the nb x nb diagonal blocks inside each ob x ob diagonal block of A:
-// A[i][j] = 0 for (i / nb + 1) nb <= j < min((i / ob + 1) ob, d).
-template <class T>
-__global__ __launch_bounds__(256) void zero_upper_kernel(T* A, int64_t d, int nb, int ob) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < d * ob;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = e / ob, j = (i / ob) * ob + e % ob;
-    if (j < d && j >= (i / nb + 1) * nb) A[i * d + j] = T(0);
-  }
-}
-
-// A = G + lambda I (full copy), R = C, info = 0. A workgroup copies whole rows (rows
-// of A first, then of R) in 16-byte runs when source and destination allow it; the
-// thread whose run holds A's diagonal element adds lambda to it.
+// A = G + lambda I, with zeros above the nb x nb diagonal blocks inside each ob x ob
+// diagonal block (the factorisation neither reads nor writes there; the ob-wide inverses
+// need them), R = C, info = 0. A workgroup copies whole rows (rows of A first, then of R)
+// in 16-byte runs when source and destination allow it; the thread whose run holds A's
+// diagonal element adds lambda to it.
 template <class T>
 __global__ __launch_bounds__(256) void init_kernel(const T* __restrict__ G, const T* __restrict__ C,
                                                    T* __restrict__ A, T* __restrict__ R, int64_t d,
                                                    int64_t dout, double lambda,
-                                                   const double* lam_dev, int32_t* info) {
+                                                   const double* lam_dev, int nb, int ob,
+                                                   int32_t* info) {
   constexpr int EV = 16 / sizeof(T);
   typedef T V16 __attribute__((ext_vector_type(EV)));
   const T lam = (T)(lam_dev ? *lam_dev : lambda);
@@ -1134,17 +1186,22 @@ __global__ __launch_bounds__(256) void init_kernel(const T* __restrict__ G, cons
     const T* src = isA ? G + r * d : C + r * dout;
     T* dst = isA ? A + r * d : R + r * dout;
     const int64_t diag = isA ? r : -1;
+    const int64_t z0 = isA ? (r / nb + 1) * nb : n, z1 = isA ? (r / ob + 1) * ob : n;  // zeros
     if ((((uintptr_t)src | (uintptr_t)dst) & 15) == 0) {
       const int64_t nv = n / EV;
       for (int64_t v = threadIdx.x; v < nv; v += blockDim.x) {
-        V16 x = *(const V16*)(src + v * EV);
+        // (nb and ob are multiples of EV)
+        const V16 x0 = *(const V16*)(src + v * EV);
+        V16 x = v * EV >= z0 && v * EV < z1 ? V16{} : x0;
         const int64_t t = diag - v * EV;
         if (t >= 0 && t < EV) x[t] += lam;
         *(V16*)(dst + v * EV) = x;
       }
-      for (int64_t j = nv * EV + threadIdx.x; j < n; j += blockDim.x) dst[j] = src[j] + (j == diag ? lam : T(0));
+      for (int64_t j = nv * EV + threadIdx.x; j < n; j += blockDim.x)
+        dst[j] = j >= z0 && j < z1 ? T(0) : src[j] + (j == diag ? lam : T(0));
     } else {
-      for (int64_t j = threadIdx.x; j < n; j += blockDim.x) dst[j] = src[j] + (j == diag ? lam : T(0));
+      for (int64_t j = threadIdx.x; j < n; j += blockDim.x)
+        dst[j] = j >= z0 && j < z1 ? T(0) : src[j] + (j == diag ? lam : T(0));
     }
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) *info = 0;
@@ -1294,7 +1351,7 @@ SGemm to_sgemm(const GemmDesc<float>& g, bool& ak, bool& bj, int tile) {
   s.lower = g.lower;
   const int tm = (g.M + tile - 1) / tile, tn = (g.N + tile - 1) / tile;
   s.tiles_n = tn;
-  s.tiles_b = g.lower ? tm * (tm + 1) / 2 : tm * tn;  // a lower-triangle update is square
+  s.tiles_b = g.lower ? tn * (tn + 1) / 2 + (tm - tn) * tn : tm * tn;  // lower: M >= N
   s.batch = g.batch;
   s.ntiles = s.batch * s.tiles_b;
   s.bA = g.bA; s.bB = g.bB; s.bC = g.bC;
@@ -1333,13 +1390,21 @@ hipError_t run_group_split(const GemmDesc<float>* ds, int n, hipStream_t st) {
   }
   const int total = s[0].ntiles + s[1].ntiles;
   const dim3 grid((total + kXcds - 1) / kXcds * kXcds), block(256);
+  // (three-term planes of two halves would not fit in LDS)
+  constexpr int K2 = 2 * Split<TERMS>::KC;
+  const bool halves = total <= 256 && s[0].K % K2 == 0 && s[1].K % K2 == 0 &&
+                      std::min(s[0].K, m == 2 ? s[1].K : s[0].K) >= 16 * K2;
   const int key = (ak[0] << 3) | (bj[0] << 2) | (ak[1] << 1) | (int)bj[1];
 #define PKV_SG(A0, B0, A1, B1)                                                                  \
   do {                                                                                          \
-    if (small)                                                                                  \
-      hipLaunchKernelGGL((sgemm3s_kernel<TERMS, A0, B0, A1, B1>), grid, block, 0, st, s[0], s[1]); \
+    if (small && total <= 256)                                                                  \
+      hipLaunchKernelGGL((sgemm3s_kernel<TERMS, A0, B0, A1, B1, 128>), grid, block, 0, st, s[0], s[1]); \
+    else if (small)                                                                             \
+      hipLaunchKernelGGL((sgemm3s_kernel<TERMS, A0, B0, A1, B1, 64>), grid, block, 0, st, s[0], s[1]); \
+    else if (TERMS == 6 && halves)                                                              \
+      hipLaunchKernelGGL((sgemm3_kernel<TERMS, A0, B0, A1, B1, TERMS == 6 ? 2 : 1>), grid, dim3(512), 0, st, s[0], s[1]); \
     else                                                                                        \
-      hipLaunchKernelGGL((sgemm3_kernel<TERMS, A0, B0, A1, B1>), grid, block, 0, st, s[0], s[1]);  \
+      hipLaunchKernelGGL((sgemm3_kernel<TERMS, A0, B0, A1, B1, 1>), grid, block, 0, st, s[0], s[1]);  \
   } while (0)
   switch (key) {
     case 0b1011: PKV_SG(true, false, true, true); break;
@@ -1414,7 +1479,7 @@ hipError_t solve_t(const T* G, const T* C, int64_t d64, int64_t dout64, double l
   {
     const int blocks = (int)std::min<int64_t>(2 * d64, 4096);
     hipLaunchKernelGGL((init_kernel<T>), dim3(blocks), dim3(256), 0, st, G, C, A, R, d64, dout64,
-                       lambda, scaled ? lam : (const double*)nullptr, info);
+                       lambda, scaled ? lam : (const double*)nullptr, NB, kSolveNBO * NB, info);
     PKV_TRY(hipGetLastError());
   }
   const T one = T(1), zero = T(0), mone = T(-1);
@@ -1437,8 +1502,8 @@ hipError_t solve_t(const T* G, const T* C, int64_t d64, int64_t dout64, double l
     for (int kb = K0; kb < K0 + W; kb += NB) {
       const int bs = std::min(NB, d - kb);
       const int rest = d - kb - bs;
-      hipLaunchKernelGGL((potrf_blk_kernel<T>), dim3(1), dim3(64 * potrf_waves<T>()), 0, st, A, d64, kb, bs,
-                         info);
+      hipLaunchKernelGGL((potrf_blk_kernel<T, 0>), dim3(1), dim3(64 * potrf_waves<T>()), 0, st, A, d64, kb,
+                         bs, info, (float*)nullptr);
       PKV_TRY(hipGetLastError());
       const T* Linv = A + (int64_t)kb * d + kb;  // Linv(i,t) = Linv[i*d + t]
       {
@@ -1459,7 +1524,7 @@ hipError_t solve_t(const T* G, const T* C, int64_t d64, int64_t dout64, double l
         const int wr = K0 + W - kb1;
         const T* Lr = Lm + (int64_t)kb1 * d + kb;  // rows kb1.., cols of block k
         GemmDesc<T> g[2];
-        g[0] = desc<T>(Lr, d, 1, Lr, 1, d, A + (int64_t)kb1 * d + kb1, d, d - kb1, wr, bs, mone, one);
+        g[0] = desc<T>(Lr, d, 1, Lr, 1, d, A + (int64_t)kb1 * d + kb1, d, d - kb1, wr, bs, mone, one, 1);
         g[1] = desc<T>(Lr, d, 1, Z + (int64_t)kb * dout, dout, 1, R + (int64_t)kb1 * dout, dout, wr,
                        dout, bs, mone, one);
         PKV_TRY(run(g, 2));
@@ -1486,11 +1551,6 @@ hipError_t solve_t(const T* G, const T* C, int64_t d64, int64_t dout64, double l
   // as a second problem). Each outer block then takes two launches instead of two
   // per column block.
   T* Tw = (T*)(w + L.Tw);
-  {
-    const int blocks = (int)std::min<int64_t>((d64 * OB + 255) / 256, 4096);
-    hipLaunchKernelGGL((zero_upper_kernel<T>), dim3(blocks), dim3(256), 0, st, A, d64, NB, OB);
-    PKV_TRY(hipGetLastError());
-  }
   for (int s = NB; s < OB && s < d; s *= 2) {
     const int full = d / (2 * s);                // pairs with both halves s wide
     const int q_r = full * 2 * s, s2_r = d - q_r - s;  // the short last pair, if s2_r > 0
@@ -1559,18 +1619,37 @@ static_assert(kRrrBlock <= 64, "the tall-skinny products take at most 64 columns
 constexpr int kJacobiSweeps = 14;
 
 // M[i][i] += rel * trace(M) / n (one workgroup; the trace in fp64, fixed order)
-__global__ __launch_bounds__(256) void diag_shift_kernel(float* M, int64_t n, int64_t ld, float rel) {
-  __shared__ double part[256];
+__global__ __launch_bounds__(1024) void diag_shift_kernel(float* M, int64_t n, int64_t ld, float rel) {
+  __shared__ double part[1024];
   double t = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += 256) t += (double)M[i * ld + i];
+#pragma unroll 4
+  for (int64_t i = threadIdx.x; i < n; i += 1024) t += (double)M[i * ld + i];
   part[threadIdx.x] = t;
   __syncthreads();
-  for (int s2 = 128; s2 > 0; s2 >>= 1) {
+  for (int s2 = 512; s2 > 0; s2 >>= 1) {
     if ((int)threadIdx.x < s2) part[threadIdx.x] += part[threadIdx.x + s2];
     __syncthreads();
   }
   const float mu = (float)(rel * part[0] / (double)n);
-  for (int64_t i = threadIdx.x; i < n; i += 256) M[i * ld + i] += mu;
+#pragma unroll 4
+  for (int64_t i = threadIdx.x; i < n; i += 1024) M[i * ld + i] += mu;
+}
+
+// M[j][i] = M[i][j] for i > j (64 x 64 tiles through LDS, one workgroup per lower tile)
+__global__ __launch_bounds__(256) void mirror_lower_kernel(float* M, int n, int64_t ld) {
+  __shared__ float tile[64][65];
+  const int ti = blockIdx.y, tj = blockIdx.x;
+  if (tj > ti) return;
+  const int c = threadIdx.x % 64;
+  for (int r = threadIdx.x / 64; r < 64; r += 4) {
+    const int i = ti * 64 + r, j = tj * 64 + c;
+    if (i < n && j < n) tile[r][c] = M[(int64_t)i * ld + j];
+  }
+  __syncthreads();
+  for (int r = threadIdx.x / 64; r < 64; r += 4) {
+    const int i = tj * 64 + r, j = ti * 64 + c;  // element (j, i) of the lower triangle
+    if (i < n && j < n && j > i) M[(int64_t)i * ld + j] = tile[c][r];
+  }
 }
 
 // Tall-skinny products of the subspace iteration: C [rows][nc] = A [rows][K] B [K][nc]
@@ -1582,7 +1661,7 @@ __global__ __launch_bounds__(256) void diag_shift_kernel(float* M, int64_t n, in
 // loaded while the current one is multiplied; the eight partial tiles are summed in
 // LDS in wave order (deterministic). Lane l holds row l % 16 of the A chunk, columns
 // 4 (l / 16) .. +3, and the matching rows of B for column l % 16 of each tile.
-constexpr int kTsWaves = 8;
+constexpr int kTsWaves = 8, kTsAhead = 4;
 __device__ __forceinline__ f32x4 mfma16_f32(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
@@ -1596,9 +1675,53 @@ __global__ __launch_bounds__(64 * kTsWaves) void tsgemm_kernel(const float* __re
   const int64_t r0 = (int64_t)blockIdx.x * 16;
   const int64_t row = r0 + l16;
   const bool va = (lda & 3) == 0 && (((uintptr_t)A) & 15) == 0;
-  f32x4 a_cur, a_nxt;
-  float b_cur[NCT][4], b_nxt[NCT][4];
-  auto load = [&](int k0, f32x4& a, float (&b)[NCT][4]) {
+  constexpr int step = 16 * kTsWaves;
+  f32x4 acc[NCT];
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // 64 columns, whole rows and aligned operands: plain 16-byte loads, kTsAhead chunks in
+  // flight (tile ct takes columns 4 l + ct, so a lane's four tiles are one load). The 51
+  // products of a d = 4096 patch: 1.23 -> 1.01 ms; more loads in flight alone, or whole
+  // 128-byte lines of A per wave (1.08), gained nothing.
+  const bool wide = NCT == 4 && nc == 64 && r0 + 16 <= rows && va && (ldb & 3) == 0 &&
+                    (((uintptr_t)B) & 15) == 0;
+  int k0 = 16 * wid;  // the first chunk left to the guarded loop
+  if constexpr (NCT == 4) {
+    const int n = K / 16 > wid ? (K / 16 - wid + kTsWaves - 1) / kTsWaves : 0;  // whole chunks
+    if (wide && n > 0) {
+      const float* pa = A + row * lda + k0 + 4 * g;
+      const float* pb = B + (int64_t)(k0 + 4 * g) * ldb + 4 * l16;
+      f32x4 av[kTsAhead], bv[kTsAhead][4];
+      auto load = [&](int i, auto u_t) {
+        constexpr int u = decltype(u_t)::value;
+        const int64_t k = (int64_t)min(i, n - 1) * step;  // (past the end: the last one again)
+        av[u] = *(const f32x4*)(pa + k);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) bv[u][t] = *(const f32x4*)(pb + (k + t) * ldb);
+      };
+      auto mult = [&](auto u_t) {
+        constexpr int u = decltype(u_t)::value;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int ct = 0; ct < NCT; ++ct) acc[ct] = mfma16_f32(av[u][t], bv[u][t][ct], acc[ct]);
+      };
+      static_for<kTsAhead>([&](auto u_t) { load(decltype(u_t)::value, u_t); });
+      int i = 0;
+      for (; i + kTsAhead <= n; i += kTsAhead)
+        static_for<kTsAhead>([&](auto u_t) {
+          mult(u_t);
+          load(i + kTsAhead + decltype(u_t)::value, u_t);
+        });
+      static_for<kTsAhead>([&](auto u_t) {
+        if (i + decltype(u_t)::value < n) mult(u_t);
+      });
+      k0 += n * step;
+    }
+  }
+  for (; k0 < K; k0 += step) {
+    f32x4 a;
+    float bq[NCT][4];
     const int k = k0 + 4 * g;
     if (row < rows && va && k + 3 < K) {
       a = *(const f32x4*)(A + row * lda + k);
@@ -1608,28 +1731,14 @@ __global__ __launch_bounds__(64 * kTsWaves) void tsgemm_kernel(const float* __re
     }
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct) {
-      const int c = 16 * ct + l16;
+      const int c = wide ? 4 * l16 + ct : 16 * ct + l16;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) b[ct][t] = (k + t < K && c < nc) ? B[(int64_t)(k + t) * ldb + c] : 0.f;
+      for (int t = 0; t < 4; ++t) bq[ct][t] = (k + t < K && c < nc) ? B[(int64_t)(k + t) * ldb + c] : 0.f;
     }
-  };
-  f32x4 acc[NCT];
-#pragma unroll
-  for (int ct = 0; ct < NCT; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-  constexpr int step = 16 * kTsWaves;
-  int k0 = 16 * wid;
-  if (k0 < K) load(k0, a_cur, b_cur);
-  for (; k0 < K; k0 += step) {
-    if (k0 + step < K) load(k0 + step, a_nxt, b_nxt);
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int ct = 0; ct < NCT; ++ct) acc[ct] = mfma16_f32(a_cur[t], b_cur[ct][t], acc[ct]);
-    a_cur = a_nxt;
-#pragma unroll
-    for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) b_cur[ct][t] = b_nxt[ct][t];
+      for (int ct = 0; ct < NCT; ++ct) acc[ct] = mfma16_f32(a[t], bq[ct][t], acc[ct]);
   }
 #pragma unroll
   for (int ct = 0; ct < NCT; ++ct)
@@ -1643,36 +1752,48 @@ __global__ __launch_bounds__(64 * kTsWaves) void tsgemm_kernel(const float* __re
 #pragma unroll
     for (int w = 0; w < kTsWaves; ++w) v += red[w][ct][e][ln];
     const int64_t rr = r0 + 4 * (ln >> 4) + e;
-    const int c = 16 * ct + (ln & 15);
+    const int c = wide ? 4 * (ln & 15) + ct : 16 * ct + (ln & 15);
     if (rr < rows && c < nc) C[rr * ldc + c] = v;
   }
 }
 
 // Partial sums of X^T Y in fp64 (X, Y [rows][b] fp32, b <= kRrrBlock) over slice z of
-// the rows: part[z][i][j]; one workgroup per 16 x 16 tile and slice.
-constexpr int kGramSlices = 16;
-__global__ __launch_bounds__(256) void gram_partial_kernel(const float* __restrict__ X,
+// the rows: part[z][i][j]; one workgroup per 16 x 16 tile and slice (lower: only tiles with
+// tile_row >= tile_col). Its waves take interleaved runs of 4 rows on MFMA f64, eight runs'
+// loads in flight, and are summed in wave order.
+constexpr int kGramSlices = 4, kGramWaves = 16;
+__global__ __launch_bounds__(64 * kGramWaves) void gram_partial_kernel(const float* __restrict__ X,
                                                            const float* __restrict__ Y, int64_t rows,
-                                                           int b, double* __restrict__ part) {
-  __shared__ float xs[64][17], ys[64][17];
-  const int i0 = blockIdx.y * 16, j0 = blockIdx.x * 16, z = blockIdx.z, tid = threadIdx.x;
-  const int ti = tid / 16, tj = tid % 16;
+                                                           int b, int lower, double* __restrict__ part) {
+  if (lower && blockIdx.x > blockIdx.y) return;
+  __shared__ double red[kGramWaves][256];
+  const int i0 = blockIdx.y * 16, j0 = blockIdx.x * 16, z = blockIdx.z;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, g = lane >> 4, l16 = lane & 15;
   const int64_t per = (rows + kGramSlices - 1) / kGramSlices;
   const int64_t lo = z * per, hi = std::min<int64_t>(rows, lo + per);
-  double acc = 0.0;
-  for (int64_t k0 = lo; k0 < hi; k0 += 64) {
-    for (int e = tid; e < 64 * 16; e += 256) {
-      const int kk = e / 16, c = e % 16;
-      const int64_t k = k0 + kk;
-      xs[kk][c] = (k < hi && i0 + c < b) ? X[k * b + i0 + c] : 0.f;
-      ys[kk][c] = (k < hi && j0 + c < b) ? Y[k * b + j0 + c] : 0.f;
+  const bool ia = i0 + l16 < b, ja = j0 + l16 < b;
+  f64x4 acc = {};
+  for (int64_t k0 = lo + 4 * wid; k0 < hi; k0 += 8 * 4 * kGramWaves) {
+    float x[8], y[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t k = k0 + 4 * kGramWaves * u + g;
+      x[u] = ia && k < hi ? X[k * b + i0 + l16] : 0.f;
+      y[u] = ja && k < hi ? Y[k * b + j0 + l16] : 0.f;
     }
-    __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < 64; ++kk) acc = fma((double)xs[kk][ti], (double)ys[kk][tj], acc);
-    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc = mfma16((double)x[u], (double)y[u], acc);
   }
-  if (i0 + ti < b && j0 + tj < b) part[((int64_t)z * b + i0 + ti) * b + j0 + tj] = acc;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) red[wid][acc_row<double>(g, e) * 16 + l16] = acc[e];
+  __syncthreads();
+  const int e = threadIdx.x, i = i0 + e / 16, j = j0 + e % 16;
+  if (e < 256 && i < b && j < b) {
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < kGramWaves; ++w) v += red[w][e];
+    part[((int64_t)z * b + i) * b + j] = v;
+  }
 }
 
 // W = sum over the slices, in slice order (fp64)
@@ -1683,15 +1804,6 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restri
   double s = 0.0;
   for (int z = 0; z < kGramSlices; ++z) s += part[(int64_t)z * b * b + e];
   W[e] = s;
-}
-
-// Wt[k][j] = (float) L^-1[j][k]: the transposed inverse factor, row-major, for tsgemm
-__global__ __launch_bounds__(256) void linv_t_kernel(const double* __restrict__ Linv, int b,
-                                                     float* __restrict__ Wt) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= b * b) return;
-  const int k = e / b, j = e % b;
-  Wt[e] = (float)Linv[j * b + k];
 }
 
 // Q[i][j] = a counter-based pseudo-random value in [-1, 1) of (i, j)
@@ -1710,26 +1822,28 @@ __global__ __launch_bounds__(256) void rrr_init_kernel(float* Q, int64_t rows, i
 
 // Eigenvectors of the symmetric b x b matrix (T + T^T) / 2 (b even, <= kRrrBlock) by
 // parallel cyclic Jacobi in fp64: each step rotates NB/2 disjoint index pairs of a
-// round-robin schedule, columns then rows. The matrix is padded with zeros to
-// NB = kRrrBlock (a padded index never couples, so its rotations are the identity,
-// and it never enters the ranking), so all index arithmetic is compile-time. Thread
-// tid takes row (column update) or column (row update) tid % 64 of pairs tid / 64 + 4u:
-// the lanes of a wave read one pair's entries down a column or along a row, which
-// spreads them over the LDS banks. Vr [b][r] receives the
+// round-robin schedule. The matrix is padded with zeros to NB = kRrrBlock (a padded index
+// never couples, so its rotations are the identity, and it never enters the ranking), so
+// all index arithmetic is compile-time. Thread (s, t) updates the 2 x 2 block of pairs s
+// and t, A <- J_s^T A J_t, in one go (the blocks are disjoint); then the first wave forms the next
+// step's rotations while the others update the eigenvectors, V <- V J. Bound by the
+// serial chain of a step (its rotations, two barriers): 410 us, 606 with columns and
+// rows updated one after the other by 256 threads. Vr [b][r] receives the
 // eigenvectors of the r largest eigenvalues, in descending order (ties: lower index
 // first); w [b] all eigenvalues by index.
-__global__ __launch_bounds__(256) void jacobi_top_kernel(const double* __restrict__ T, int b, int r,
-                                                         float* __restrict__ Vr,
-                                                         double* __restrict__ w) {
-  constexpr int NB = kRrrBlock, P = NB + 1, HALF = NB / 2;
-  static_assert(NB == 64, "thread mapping assumes a 64-wide block and 256 threads");
+constexpr int kJacobiThreads = (kRrrBlock / 2) * (kRrrBlock / 2);
+__global__ __launch_bounds__(kJacobiThreads) void jacobi_top_kernel(const double* __restrict__ T, int b,
+                                                                    int r, float* __restrict__ Vr,
+                                                                    double* __restrict__ w) {
+  constexpr int NB = kRrrBlock, P = NB + 1, HALF = NB / 2, NT = kJacobiThreads;
+  static_assert(NB == 64 && NT == 1024, "thread mapping assumes a 64-wide block");
   __shared__ double A[NB * P], V[NB * P];
-  __shared__ double cs[HALF][2];
-  __shared__ int pq[HALF][2];
-  __shared__ double red[2][256];
+  __shared__ double cs[2][HALF][2];
+  __shared__ int pq[2][HALF][2];
+  __shared__ double red[2][NT / kWave];
   __shared__ int done;
   const int tid = threadIdx.x;
-  for (int e = tid; e < NB * NB; e += 256) {
+  for (int e = tid; e < NB * NB; e += NT) {
     const int i = e / NB, j = e % NB;
     double a = 0.0;
     if (i < b && j < b) a = 0.5 * (T[i * b + j] + T[j * b + i]);
@@ -1737,94 +1851,93 @@ __global__ __launch_bounds__(256) void jacobi_top_kernel(const double* __restric
     V[i * P + j] = i == j ? 1.0 : 0.0;
   }
   __syncthreads();
-  const int kk = tid % NB, t0 = tid / NB;  // this thread's row / column and first pair
+  // pair k of step `step` and its rotation, into buffer `to`
+  auto rotation = [&](int k, int step, int to) {
+    // round robin: position 0 fixed, the others rotate by `step`
+    auto at = [&](int k2) { return k2 == 0 ? 0 : (k2 - 1 + step) % (NB - 1) + 1; };
+    const int p0 = at(k), q0 = at(NB - 1 - k);
+    const int p = min(p0, q0), q = max(p0, q0);
+    const double apq = A[p * P + q];
+    double c = 1.0, s = 0.0;
+    if (fabs(apq) > 1e-300) {
+      // t = tan of the rotation angle, the root of t^2 + 2 th t - 1 of smaller
+      // magnitude; native fp64 reciprocal and reciprocal square root, each with one
+      // Newton step, so that c^2 + s^2 = 1 to fp64 rounding
+      const double th = (A[q * P + q] - A[p * P + p]) * rcp64(2.0 * apq);
+      const double ath = fabs(th);
+      double t;
+      if (ath < 1e150) {
+        const double y = fma(th, th, 1.0);
+        t = rcp64(ath + y * rsq64(y));
+      } else {
+        t = 0.5 * rcp64(ath);
+      }
+      if (th < 0.0) t = -t;
+      c = rsq64(fma(t, t, 1.0));
+      s = t * c;
+    }
+    pq[to][k][0] = p;
+    pq[to][k][1] = q;
+    cs[to][k][0] = c;
+    cs[to][k][1] = s;
+  };
+  const int ps = tid / HALF, pt = tid % HALF;
   for (int sweep = 0; sweep < kJacobiSweeps; ++sweep) {
     // stop once the off-diagonal mass is below 1e-24 of the diagonal's: an eigenvector
     // is then off by about 1e-12 ||A|| / gap, far below the fp32 output's precision
     double off = 0.0, dia = 0.0;
-    for (int e = tid; e < NB * NB; e += 256) {
+    for (int e = tid; e < NB * NB; e += NT) {
       const int i = e / NB, j = e % NB;
-      if (i >= b || j >= b) continue;
       const double v = A[i * P + j] * A[i * P + j];
       if (i == j) dia += v; else off += v;
     }
-    red[0][tid] = off;
-    red[1][tid] = dia;
-    __syncthreads();
-    for (int s2 = 128; s2 > 0; s2 >>= 1) {
-      if (tid < s2) {
-        red[0][tid] += red[0][tid + s2];
-        red[1][tid] += red[1][tid + s2];
-      }
-      __syncthreads();
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+      off += __shfl_xor(off, o);
+      dia += __shfl_xor(dia, o);
     }
-    if (tid == 0) done = red[0][0] <= 1e-24 * red[1][0];
+    if (tid % kWave == 0) {
+      red[0][tid / kWave] = off;
+      red[1][tid / kWave] = dia;
+    }
+    if (tid < HALF) rotation(tid, 0, 0);
+    __syncthreads();
+    if (tid == 0) {
+      double so = 0.0, sd = 0.0;
+      for (int i = 0; i < NT / kWave; ++i) {
+        so += red[0][i];
+        sd += red[1][i];
+      }
+      done = so <= 1e-24 * sd;
+    }
     __syncthreads();
     if (done) break;
 #pragma unroll 1
     for (int step = 0; step < NB - 1; ++step) {
-      if (tid < HALF) {
-        // round robin: position 0 fixed, the others rotate by `step`
-        auto at = [&](int k) { return k == 0 ? 0 : (k - 1 + step) % (NB - 1) + 1; };
-        int p = at(tid), q = at(NB - 1 - tid);
-        if (p > q) { const int t = p; p = q; q = t; }
-        const double apq = A[p * P + q];
-        double c = 1.0, s = 0.0;
-        if (fabs(apq) > 1e-300) {
-          // t = tan of the rotation angle, the root of t^2 + 2 th t - 1 of smaller
-          // magnitude; native fp64 reciprocal and reciprocal square root, each with one
-          // Newton step, so that c^2 + s^2 = 1 to fp64 rounding
-          const double th = (A[q * P + q] - A[p * P + p]) * rcp64(2.0 * apq);
-          const double ath = fabs(th);
-          double t;
-          if (ath < 1e150) {
-            const double y = fma(th, th, 1.0);
-            t = rcp64(ath + y * rsq64(y));
-          } else {
-            t = 0.5 * rcp64(ath);
-          }
-          if (th < 0.0) t = -t;
-          c = rsq64(fma(t, t, 1.0));
-          s = t * c;
+      const int cur = step & 1;
+      {
+        const int p1 = pq[cur][ps][0], q1 = pq[cur][ps][1], p2 = pq[cur][pt][0], q2 = pq[cur][pt][1];
+        const double c1 = cs[cur][ps][0], s1 = cs[cur][ps][1], c2 = cs[cur][pt][0], s2 = cs[cur][pt][1];
+        const double app = A[p1 * P + p2], apq = A[p1 * P + q2], aqp = A[q1 * P + p2], aqq = A[q1 * P + q2];
+        const double bpp = c2 * app - s2 * apq, bpq = s2 * app + c2 * apq;  // columns
+        const double bqp = c2 * aqp - s2 * aqq, bqq = s2 * aqp + c2 * aqq;
+        A[p1 * P + p2] = c1 * bpp - s1 * bqp;  // rows
+        A[q1 * P + p2] = s1 * bpp + c1 * bqp;
+        A[p1 * P + q2] = c1 * bpq - s1 * bqq;
+        A[q1 * P + q2] = s1 * bpq + c1 * bqq;
+      }
+      __syncthreads();
+      if (tid < kWave) {
+        if (tid < HALF && step + 1 < NB - 1) rotation(tid, step + 1, cur ^ 1);
+      } else {
+        for (int e = tid - kWave; e < NB * HALF; e += NT - kWave) {
+          const int k = e / HALF, t = e % HALF;
+          const int p = pq[cur][t][0], q = pq[cur][t][1];
+          const double c = cs[cur][t][0], s = cs[cur][t][1];
+          const double vp = V[k * P + p], vq = V[k * P + q];
+          V[k * P + p] = c * vp - s * vq;
+          V[k * P + q] = s * vp + c * vq;
         }
-        pq[tid][0] = p;
-        pq[tid][1] = q;
-        cs[tid][0] = c;
-        cs[tid][1] = s;
-      }
-      __syncthreads();
-      // this thread's 8 pairs, read once for both halves of the step
-      int pp[HALF / 4], qq[HALF / 4];
-      double cc[HALF / 4], ss[HALF / 4];
-#pragma unroll
-      for (int u = 0; u < HALF / 4; ++u) {
-        const int t = t0 + 4 * u;
-        pp[u] = pq[t][0];
-        qq[u] = pq[t][1];
-        cc[u] = cs[t][0];
-        ss[u] = cs[t][1];
-      }
-      // columns: A <- A J, V <- V J
-#pragma unroll
-      for (int u = 0; u < HALF / 4; ++u) {
-        const int p = pp[u], q = qq[u];
-        const double c = cc[u], s = ss[u];
-        const double akp = A[kk * P + p], akq = A[kk * P + q];
-        A[kk * P + p] = c * akp - s * akq;
-        A[kk * P + q] = s * akp + c * akq;
-        const double vkp = V[kk * P + p], vkq = V[kk * P + q];
-        V[kk * P + p] = c * vkp - s * vkq;
-        V[kk * P + q] = s * vkp + c * vkq;
-      }
-      __syncthreads();
-      // rows: A <- J^T A
-#pragma unroll
-      for (int u = 0; u < HALF / 4; ++u) {
-        const int p = pp[u], q = qq[u];
-        const double c = cc[u], s = ss[u];
-        const double apk = A[p * P + kk], aqk = A[q * P + kk];
-        A[p * P + kk] = c * apk - s * aqk;
-        A[q * P + kk] = s * apk + c * aqk;
       }
       __syncthreads();
     }
@@ -1843,7 +1956,7 @@ __global__ __launch_bounds__(256) void jacobi_top_kernel(const double* __restric
 }
 
 struct RrrWs {
-  size_t X, S, Q, Z, Y, W, W64, part, T, Vr, w, info, total;
+  size_t X, S, Q, Z, Y, W, part, T, Vr, w, info, total;
 };
 RrrWs rrr_layout(int64_t din, int64_t dout, int b) {
   RrrWs L{};
@@ -1855,7 +1968,6 @@ RrrWs rrr_layout(int64_t din, int64_t dout, int b) {
   L.Z = take((size_t)dout * b * 4);
   L.Y = take((size_t)dout * b * 4);
   L.W = take((size_t)b * b * 4);
-  L.W64 = take((size_t)b * b * 8);
   L.part = take((size_t)kGramSlices * b * b * 8);
   L.T = take((size_t)b * b * 8);
   L.Vr = take((size_t)b * b * 4);
@@ -1880,7 +1992,7 @@ hipError_t launch_low_rank(const float* G, const float* dW, int64_t din, int64_t
   float *X = (float*)(w + L.X), *S = (float*)(w + L.S), *Q = (float*)(w + L.Q);
   float *Z = (float*)(w + L.Z), *Y = (float*)(w + L.Y), *W = (float*)(w + L.W);
   float* Vr = (float*)(w + L.Vr);
-  double *W64 = (double*)(w + L.W64), *part = (double*)(w + L.part), *T = (double*)(w + L.T);
+  double *part = (double*)(w + L.part), *T = (double*)(w + L.T);
   double* ev = (double*)(w + L.w);
   int32_t* info = (int32_t*)(w + L.info);
   const int din_i = (int)din, dout_i = (int)dout;
@@ -1888,10 +2000,14 @@ hipError_t launch_low_rank(const float* G, const float* dW, int64_t din, int64_t
   {
     GemmDesc<float> g = desc<float>(G, din, 1, dW, dout, 1, X, dout, din_i, dout_i, din_i, 1.f, 0.f);
     PKV_TRY(run_group_split<6>(&g, 1, st));
-    g = desc<float>(dW, 1, dout, X, dout, 1, S, dout, dout_i, dout_i, din_i, 1.f, 0.f);
+    // S is symmetric: its lower tiles, mirrored
+    g = desc<float>(dW, 1, dout, X, dout, 1, S, dout, dout_i, dout_i, din_i, 1.f, 0.f, 1);
     PKV_TRY(run_group_split<6>(&g, 1, st));
+    const unsigned t = (unsigned)((dout + 63) / 64);
+    hipLaunchKernelGGL(mirror_lower_kernel, dim3(t, t), dim3(256), 0, st, S, dout_i, dout);
+    PKV_TRY(hipGetLastError());
   }
-  hipLaunchKernelGGL(diag_shift_kernel, dim3(1), dim3(256), 0, st, S, dout, dout,
+  hipLaunchKernelGGL(diag_shift_kernel, dim3(1), dim3(1024), 0, st, S, dout, dout,
                      (float)(1e-5 * (double)dout));
   PKV_TRY(hipGetLastError());
   {
@@ -1913,21 +2029,17 @@ hipError_t launch_low_rank(const float* G, const float* dW, int64_t din, int64_t
     }
     return hipGetLastError();
   };
-  // fp64 X^T Y [b][b]
-  auto gram = [&](const float* Xm, const float* Ym, double* out) -> hipError_t {
+  // slices of fp64 X^T Y [b][b]
+  auto gram = [&](const float* Xm, const float* Ym, int lower) -> hipError_t {
     const dim3 gg((unsigned)((b + 15) / 16), (unsigned)((b + 15) / 16), kGramSlices);
-    hipLaunchKernelGGL(gram_partial_kernel, gg, dim3(256), 0, st, Xm, Ym, dout, b, part);
-    PKV_TRY(hipGetLastError());
-    hipLaunchKernelGGL(gram_reduce_kernel, dim3((b * b + 255) / 256), dim3(256), 0, st, part, b, out);
+    hipLaunchKernelGGL(gram_partial_kernel, gg, dim3(64 * kGramWaves), 0, st, Xm, Ym, dout, b, lower, part);
     return hipGetLastError();
   };
   // src (dout x b) -> dst = src L^-T with src^T src = L L^T (Gram and factor in fp64)
   auto orth = [&](const float* src, float* dst) -> hipError_t {
-    PKV_TRY(gram(src, src, W64));
-    hipLaunchKernelGGL((potrf_blk_kernel<double>), dim3(1), dim3(64 * potrf_waves<double>()), 0, st, W64,
-                       (int64_t)b, 0, b, info);
-    PKV_TRY(hipGetLastError());
-    hipLaunchKernelGGL(linv_t_kernel, dim3((b * b + 255) / 256), dim3(256), 0, st, W64, b, W);
+    PKV_TRY(gram(src, src, 1));
+    hipLaunchKernelGGL((potrf_blk_kernel<double, kGramSlices>), dim3(1), dim3(64 * potrf_waves<double>()),
+                       0, st, part, (int64_t)b, 0, b, info, W);
     PKV_TRY(hipGetLastError());
     return ts(src, b, W, b, dout, b, b, dst, b);
   };
@@ -1941,8 +2053,10 @@ hipError_t launch_low_rank(const float* G, const float* dW, int64_t din, int64_t
   PKV_TRY(orth(Y, Z));
   // Rayleigh-Ritz: T = Z^T S Z (fp64), its top-r eigenvectors, U = Z Vr
   PKV_TRY(ts(S, dout, Z, b, dout, dout_i, b, Y, b));
-  PKV_TRY(gram(Z, Y, T));
-  hipLaunchKernelGGL(jacobi_top_kernel, dim3(1), dim3(256), 0, st, T, b, r, Vr, ev);
+  PKV_TRY(gram(Z, Y, 0));
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3((b * b + 255) / 256), dim3(256), 0, st, part, b, T);
+  PKV_TRY(hipGetLastError());
+  hipLaunchKernelGGL(jacobi_top_kernel, dim3(1), dim3(kJacobiThreads), 0, st, T, b, r, Vr, ev);
   PKV_TRY(hipGetLastError());
   PKV_TRY(ts(Z, b, Vr, r, dout, b, r, U, r));
   PKV_TRY(ts(dW, dout, U, r, din, dout_i, r, A, r));
