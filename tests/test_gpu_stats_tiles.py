@@ -72,3 +72,13 @@ def test_features_unaligned_rows_of_weights():
     a = pkv.mlp_features(Z, Wg, Wu)
     b = pkv.mlp_features(torch.cat([Z] * 8), Wg, Wu)  # 1,600 rows: transposed copies
     assert torch.equal(a, b[:M])
+
+
+def test_rounds_split_over_two_shapes():
+    """3.1 rounds of 256-tiles: whole rounds and the rest as two launches, residual included."""
+    M, din, dout = 4096 * 3 + 300, 40, 4096
+    Hf, Hc, W = normal(21, M, din), normal(22, M, din), normal(23, din, dout, dtype=torch.bfloat16)
+    Zf, Zc = normal(24, M, dout), normal(25, M, dout)
+    T = pkv.compute_block_targets(Hf, Hc, W, Zf, Zc)
+    ref = (Hf.double() - Hc.double()) @ W.double() + (Zf.double() - Zc.double())
+    assert float((T.double() - ref).norm() / ref.norm()) <= TOL
