@@ -5,7 +5,8 @@
 //   for each block column k:
 //     diagonal kernel    L_kk^{-1} (1 WG)
 //     grouped GEMM       L_ik = A_ik L_kk^{-T} (i > k);  Z_k = L_kk^{-1} R_k
-//     grouped GEMM       A_ij -= L_ik L_jk^T (lower blocks);  R_i -= L_ik Z_k (i > k)
+//     grouped GEMM       A_ij -= L_ik L_jk^T (lower blocks);  R_i -= L_ik Z_k (i > k);
+//                        in fp32 the next block's diagonal kernel is its first workgroup
 // The updates outside a group of eight block columns (an outer block, OB = 8 NB) are
 // deferred to the end of the group (K = OB), see solve_t. Backward substitution runs
 // per outer block: X_O = L_OO^{-T} Z_O;  Z_i -= L_Oi^T X_O (i before O).
@@ -569,13 +570,13 @@ struct TLayout {
 };
 
 template <int TERMS, bool AK, bool BJ, int KS>
-__device__ __forceinline__ void sgemm3s_body(const SGemm& g, int t, __bf16* lds) {
+__device__ __forceinline__ void sgemm3s_body(const SGemm& g, int t, __bf16* lds, bool store = true) {
   using LY = TLayout<KS>;
   constexpr int NP = Split<TERMS>::P;
   int ti, tj;
   tile_of(g, t, ti, tj);
   const int i0 = ti * T_BM, j0 = tj * T_BM;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int tid = threadIdx.x & 255, lane = tid & 63, wid = tid >> 6;
   const int h32 = lane >> 5, l32 = lane & 31;
   const int wi = (wid >> 1) * 32, wj = (wid & 1) * 32;
   constexpr bool a_rk = AK, b_rk = !BJ;
@@ -684,6 +685,7 @@ __device__ __forceinline__ void sgemm3s_body(const SGemm& g, int t, __bf16* lds)
     }
     if (k0 + KS < Kp) __syncthreads();
   }
+  if (!store) return;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int i = i0 + wi + l32, j = j0 + wj + 8 * q + 4 * h32;
@@ -1028,19 +1030,26 @@ constexpr int kLeaf = 16;       // leaf width
 // over SLICES partial blocks, added in order, from A on, and L^{-T} goes to Wt [bs][bs] in
 // fp32: 16.1 us for 4 slices, 21.7 with a launch each for the sum and the transpose (with
 // 16 slices the one workgroup's 512 KB of loads took it to 32 us).
-template <class T, int SLICES>
-__global__ __launch_bounds__(64 * potrf_waves<T>()) void potrf_blk_kernel(T* A, int64_t lda, int kb, int bs,
-                                                                    int32_t* info, float* Wt) {
+// TERMS > 0 (fp32): the block first takes its update by the block column before it,
+// A -= Lr Lr^T (Lr: its NB-wide rows of L, leading dimension lda), as the split products do.
+// lds holds potrf_lds<T>() elements.
+template <class T>
+constexpr int potrf_lds() { return 2 * Blk<T>::NB * diag_pitch<T>(); }
+template <class T, int SLICES, int TERMS>
+__device__ __forceinline__ void potrf_body(T* A, int64_t lda, int kb, int bs, int32_t* info, float* Wt,
+                                           const T* Lr, T* lds) {
   constexpr int NB = Blk<T>::NB, PT = diag_pitch<T>(), NW = potrf_waves<T>(), NT = 64 * NW;
   constexpr int EV = 16 / sizeof(T), NL = NB * NB / EV / NT;  // 16-byte pieces per thread
   constexpr int NLV = NB / kLeaf, NL1 = NLV - 1;
   typedef T V16 __attribute__((ext_vector_type(EV)));
-  __shared__ __attribute__((aligned(16))) T As[NB * PT];
-  __shared__ __attribute__((aligned(16))) T Es[NB * PT];
+  T* const As = lds;
+  T* const Es = lds + NB * PT;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   // 16-byte accesses when every row start is 16-byte aligned (kb is a multiple of NB)
   const bool vec = (lda * (int64_t)sizeof(T)) % 16 == 0 && (((uintptr_t)A) & 15) == 0;
   T* Ab = A + (int64_t)kb * lda + kb;
+  const int ui = wid < 1 ? 0 : wid < 3 ? 1 : wid < 6 ? 2 : 3, uj = wid - ui * (ui + 1) / 2;
+  f32x16 upd = {};
   {
     // every load in flight before the first LDS write; both triangles are copied
     // (the leaf reads whole rows of its diagonal block), identity past bs
@@ -1070,6 +1079,44 @@ __global__ __launch_bounds__(64 * potrf_waves<T>()) void potrf_blk_kernel(T* A, 
         }
       }
     }
+    if constexpr (TERMS > 0) {
+      // Lr's bf16 planes through the same LDS; wave w < 10 forms 32 x 32 lower tile w
+      constexpr int NP = Split<TERMS>::P, PL = NB + 8, NR = NB * NB / 4 / NT;
+      static_assert(NP * NB * PL * 2 <= potrf_lds<T>() * (int)sizeof(T), "the planes fit");
+      __bf16* pl[NP];
+#pragma unroll
+      for (int q = 0; q < NP; ++q) pl[q] = (__bf16*)lds + q * NB * PL;
+      const bool vl = (lda & 3) == 0 && (((uintptr_t)Lr) & 15) == 0;
+      f32x4 r[NR];
+#pragma unroll
+      for (int u = 0; u < NR; ++u) {
+        const int i = (u * NT + tid) / (NB / 4), k = (u * NT + tid) % (NB / 4) * 4;
+        const float* src = Lr + (int64_t)i * lda + k;
+        r[u] = f32x4{};
+        if (i < bs) {
+          if (vl) r[u] = *(const f32x4*)src;
+          else
+            for (int t = 0; t < 4; ++t) r[u][t] = src[t];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < NR; ++u)
+        split_store<NP>(pl, (u * NT + tid) / (NB / 4) * PL + (u * NT + tid) % (NB / 4) * 4, r[u]);
+      __syncthreads();
+      if (wid < 10) {
+        const int h32 = lane >> 5, l32 = lane & 31;
+        for (int ks = 0; ks < NB; ks += 16) {
+          bf16x8 fa[NP], fb[NP];
+#pragma unroll
+          for (int q = 0; q < NP; ++q) {
+            fa[q] = *(const bf16x8*)(pl[q] + (32 * ui + l32) * PL + ks + 8 * h32);
+            fb[q] = *(const bf16x8*)(pl[q] + (32 * uj + l32) * PL + ks + 8 * h32);
+          }
+          upd = split_mfma<TERMS>(fb, fa, upd);
+        }
+      }
+      __syncthreads();
+    }
 #pragma unroll
     for (int u = 0; u < NL; ++u) {
       const int e = (u * NT + tid) * EV;
@@ -1091,6 +1138,16 @@ __global__ __launch_bounds__(64 * potrf_waves<T>()) void potrf_blk_kernel(T* A, 
     }
   }
   __syncthreads();
+  if constexpr (TERMS > 0) {
+    if (wid < 10) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          As[(32 * ui + (lane & 31)) * PT + 32 * uj + 8 * q + 4 * (lane >> 5) + e] -= upd[4 * q + e];
+    }
+    __syncthreads();
+  }
   auto blk = [](T* base, int i, int j) { return base + (kLeaf * i) * PT + kLeaf * j; };
   bool failed = false;
   if (wid == 0) leaf16<T>(sym16<T>(blk(As, 0, 0), lane), blk(Es, 0, 0), lane, kb, kb + bs, info, failed);
@@ -1164,6 +1221,39 @@ __global__ __launch_bounds__(64 * potrf_waves<T>()) void potrf_blk_kernel(T* A, 
       for (int t = 0; t < EV; ++t)
         if (j0 + t < bs) dst[t] = v[t];
   }
+}
+
+template <class T, int SLICES>
+__global__ __launch_bounds__(64 * potrf_waves<T>()) void potrf_blk_kernel(T* A, int64_t lda, int kb, int bs,
+                                                                    int32_t* info, float* Wt) {
+  __shared__ __attribute__((aligned(16))) T lds[potrf_lds<T>()];
+  potrf_body<T, SLICES, 0>(A, lda, kb, bs, info, Wt, (const T*)nullptr, lds);
+}
+
+// The update of an outer block's remaining columns by one block column (d0, d1: 64 x 64 tiles,
+// K = NB) and the factorisation of the next diagonal block in one launch: workgroup 0 takes
+// the diagonal block's own update and factors it while the others, four tiles of 256
+// threads each, update the rest (without the diagonal block's tiles, the first `skip` of
+// d0). Only the factorisation is on the critical path, and its launch and loads overlap:
+// 25 us per block column at d = 4096, 17 + 14 as two launches.
+template <int TERMS>
+__global__ __launch_bounds__(1024) void update_potrf_kernel(SGemm d0, SGemm d1, int skip, float* A,
+                                                            int64_t lda, int kb, int bs, int32_t* info,
+                                                            const float* Lr) {
+  constexpr int NP = Split<TERMS>::P, KS = 32, TL = 2 * NP * TLayout<KS>::TILE;  // bf16 per tile
+  static_assert(potrf_waves<float>() == 16, "1024 threads");
+  constexpr int BYTES = potrf_lds<float>() * 4 > 4 * TL * 2 ? potrf_lds<float>() * 4 : 4 * TL * 2;
+  __shared__ __attribute__((aligned(16))) char lds[BYTES];
+  if (blockIdx.x == 0) {
+    potrf_body<float, 0, TERMS>(A, lda, kb, bs, info, (float*)nullptr, Lr, (float*)lds);
+    return;
+  }
+  // (a group past the last tile repeats it without storing: every group meets the barriers)
+  const int sub = threadIdx.x >> 8, n0 = d0.ntiles - skip, total = n0 + d1.ntiles;
+  const int t = (blockIdx.x - 1) * 4 + sub, u = min(t, total - 1);
+  __bf16* l = (__bf16*)lds + sub * TL;
+  if (u < n0) sgemm3s_body<TERMS, true, false, KS>(d0, u + skip, l, t < total);
+  else sgemm3s_body<TERMS, true, true, KS>(d1, u - n0, l, t < total);
 }
 
 // A = G + lambda I, with zeros above the nb x nb diagonal blocks inside each ob x ob
@@ -1417,6 +1507,19 @@ hipError_t run_group_split(const GemmDesc<float>* ds, int n, hipStream_t st) {
   return hipGetLastError();
 }
 
+// g[0], g[1] (an update by block column kb - NB) and the diagonal block at kb in one launch
+template <int TERMS>
+hipError_t run_update_potrf(const GemmDesc<float>* g, float* A, int64_t lda, int kb, int bs,
+                            int32_t* info, const float* Lr, hipStream_t st) {
+  bool ak, bj;
+  const SGemm s0 = to_sgemm(g[0], ak, bj, T_BM), s1 = to_sgemm(g[1], ak, bj, T_BM);
+  const int skip = bs > T_BM ? 3 : 1;  // the diagonal block's tiles lead the lower order
+  const int total = s0.ntiles - skip + s1.ntiles;
+  hipLaunchKernelGGL(update_potrf_kernel<TERMS>, dim3(1 + (total + 3) / 4), dim3(1024), 0, st, s0, s1, skip,
+                     A, lda, kb, bs, info, Lr);
+  return hipGetLastError();
+}
+
 // Column blocks of NB are grouped into outer blocks of kSolveNBO * NB (1024 wide in fp32;
 // solve at d = 4096: 2.46 ms, 4 column blocks: 2.53, 16: 2.59)
 constexpr int kSolveNBO = 8;
@@ -1499,12 +1602,16 @@ hipError_t solve_t(const T* G, const T* C, int64_t d64, int64_t dout64, double l
   const int OB = NBO * NB;
   for (int K0 = 0; K0 < d; K0 += OB) {
     const int W = std::min(OB, d - K0);  // width of this outer block
+    bool factored = false;  // the diagonal block was factored with the update before it
     for (int kb = K0; kb < K0 + W; kb += NB) {
       const int bs = std::min(NB, d - kb);
       const int rest = d - kb - bs;
-      hipLaunchKernelGGL((potrf_blk_kernel<T, 0>), dim3(1), dim3(64 * potrf_waves<T>()), 0, st, A, d64, kb,
-                         bs, info, (float*)nullptr);
-      PKV_TRY(hipGetLastError());
+      if (!factored) {
+        hipLaunchKernelGGL((potrf_blk_kernel<T, 0>), dim3(1), dim3(64 * potrf_waves<T>()), 0, st, A, d64,
+                           kb, bs, info, (float*)nullptr);
+        PKV_TRY(hipGetLastError());
+      }
+      factored = false;
       const T* Linv = A + (int64_t)kb * d + kb;  // Linv(i,t) = Linv[i*d + t]
       {
         GemmDesc<T> g[2];
@@ -1527,6 +1634,16 @@ hipError_t solve_t(const T* G, const T* C, int64_t d64, int64_t dout64, double l
         g[0] = desc<T>(Lr, d, 1, Lr, 1, d, A + (int64_t)kb1 * d + kb1, d, d - kb1, wr, bs, mone, one, 1);
         g[1] = desc<T>(Lr, d, 1, Z + (int64_t)kb * dout, dout, 1, R + (int64_t)kb1 * dout, dout, wr,
                        dout, bs, mone, one);
+        if constexpr (sizeof(T) == 4) {
+          if (products != kProductsExact) {
+            const int bs1 = std::min(NB, d - kb1);
+            PKV_TRY(products == kProductsSplit6
+                        ? run_update_potrf<6>(g, A, d64, kb1, bs1, info, Lr, st)
+                        : run_update_potrf<3>(g, A, d64, kb1, bs1, info, Lr, st));
+            factored = true;
+            continue;
+          }
+        }
         PKV_TRY(run(g, 2));
       }
     }
