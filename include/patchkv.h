@@ -168,7 +168,7 @@ int patchkv_attend_compressed(int dtype, const void* Q, const void* K, const voi
 /* capture, tight serving loops (e.g. re-patching after each online compaction  */
 /* of the cache), harnesses that forbid hipMalloc. Same arguments and results   */
 /* as patchkv_attend_compressed, without the workspace: the scratch (V^T tiles, */
-/* fast-path flags, split-key partials) lives in one fixed device buffer of     */
+/* split-key partials) lives in one fixed device buffer of                    */
 /* PATCHKV_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on */
 /* until the process ends. The call allocates nothing (no hipMalloc, no         */
 /* allocating library routine). A shape whose scratch                           */

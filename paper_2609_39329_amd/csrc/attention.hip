@@ -75,37 +75,51 @@ AttnPlan plan_attention(const AttnShape& s) {
   // own entries (tiles of a row tile's causal prefix, longest and on average): work items
   // of a short cache differ in length and are handed out longest first, which takes about
   // the total over the CUs plus half of a shortest item; where the cache range is the
-  // longer part they run in rounds
+  // longer part they run in rounds. That estimate chooses among the counts up to the one
+  // that rounds alone give (best_r): the workspace holds best_r ranges' partial results, so
+  // its size does not depend on the estimate.
   const int64_t own_max = (s.Ms + kt - 1) / kt;
-  double best = 1e300;
-  int best_s = 1;
-  for (int sp = 1; sp <= 64 && sp <= ntiles; ++sp) {
-    const int64_t tps = (ntiles + sp - 1) / sp;
-    const int64_t waves = (items * sp + (int64_t)slots - 1) / (int64_t)slots;
-    double cost = (double)waves * tps * tile_s;
-    if (s.bf16 && tps < own_max)
-      cost = tile_s * std::max((double)items * (ntiles + 0.5 * own_max) / slots + 0.5 * tps,
-                               (double)(tps + own_max));
-    if (sp > 1) cost += (double)s.Hkv * rows * (s.dh + 2) * 4.0 * sp * 2 / 4e12 + 4e-6;
-    if (cost < best * 0.98) {
-      best = cost;
-      best_s = sp;
+  auto ranges = [&](int limit, bool own) {
+    double best = 1e300;
+    int best_s = 1;
+    for (int sp = 1; sp <= limit && sp <= ntiles; ++sp) {
+      const int64_t tps = (ntiles + sp - 1) / sp;
+      const int64_t waves = (items * sp + (int64_t)slots - 1) / (int64_t)slots;
+      double cost = (double)waves * tps * tile_s;
+      if (own && tps < own_max)
+        cost = tile_s * std::max((double)items * (ntiles + 0.5 * own_max) / slots + 0.5 * tps,
+                                 (double)(tps + own_max));
+      if (sp > 1) cost += (double)s.Hkv * rows * (s.dh + 2) * 4.0 * sp * 2 / 4e12 + 4e-6;
+      if (cost < best * 0.98) {
+        best = cost;
+        best_s = sp;
+      }
     }
-  }
+    return best_s;
+  };
+  auto count = [&](int sp) {  // non-empty ranges of whole tiles
+    const int64_t tps = (ntiles + sp - 1) / sp;
+    return (int)((ntiles + tps - 1) / tps);
+  };
+  const int best_r = ranges(64, false);
+  const int best_s = s.bf16 && own_max > 0 ? ranges(best_r, true) : best_r;
   const int64_t tps = (ntiles + best_s - 1) / best_s;
   pl.keys_per_split = (int)(tps * kt);
-  pl.n_split = (int)((s.Nk + pl.keys_per_split - 1) / pl.keys_per_split);
+  pl.n_split = count(best_s);
   pl.total_items = (int)(items * pl.n_split);
   pl.per_xcd = (pl.total_items + kXcds - 1) / kXcds;
   pl.grid = pl.per_xcd * kXcds;
-  pl.ws_bytes = pl.n_split > 1
-                    ? align_up((size_t)s.Hkv * pl.n_split * rows * s.dh * sizeof(float)) +
-                          align_up((size_t)s.Hkv * pl.n_split * rows * 2 * sizeof(float))
-                    : 0;
+  const int n_ws = std::max(count(best_r), pl.n_split);
+  pl.ws_bytes = n_ws > 1 ? align_up((size_t)s.Hkv * n_ws * rows * s.dh * sizeof(float)) +
+                               align_up((size_t)s.Hkv * n_ws * rows * 2 * sizeof(float))
+                         : 0;
   if (s.bf16) {
     pl.ws_bytes += align_up((size_t)s.Hkv * ntiles * 32 * s.dh * 2);  // V^T tiles
     if (s.Ms > 0)  // V^T tiles of the own entries
       pl.ws_bytes += align_up((size_t)s.Hkv * ((s.Ms + kKeyTile - 1) / kKeyTile) * 32 * s.dh * 2);
+    // one word per work item, unused: the size of the interface, which buffers of callers
+    // and the limit of the fixed scratch follow
+    pl.ws_bytes += align_up((size_t)items * n_ws * sizeof(int));
   }
   return pl;
 }

@@ -36,7 +36,7 @@ from collections import defaultdict
 ROOT = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ["paper_2609_39329_amd/csrc/attention_kernels.hpp",
            "paper_2609_39329_amd/csrc/attention.hip", "paper_2609_39329_amd/csrc/stats.hip",
-           "paper_2609_39329_amd/csrc/solve.hip"]
+           "paper_2609_39329_amd/csrc/solve.hip", "paper_2609_39329_amd/csrc/gemm_f64.hpp"]
 PEAK_GBS = 8000.0
 LIB_KERNEL = re.compile(r"pkv::|^_ZN3pkv")
 COPY_KERNEL = re.compile(r"copy|elementwise", re.I)
@@ -259,15 +259,13 @@ def main() -> None:
                 line += " – | – | – |"
         print(line)
 
-    # the full-cache pass: the teacher's fast path and its fixup (one dispatch each per
-    # layer or reference chunk: no other call uses these instantiations; a chunk's pass
-    # carries its own entries; the teacher reads its contiguous cache's V as stored, so no
-    # V^T pre-pass belongs to it), with split key ranges the merge (its largest dispatch),
+    # the full-cache pass: the teacher's kernel (one dispatch per layer or reference chunk:
+    # no other call uses this instantiation; a chunk's pass carries its own entries; the
+    # teacher reads its contiguous cache's V as stored, so no V^T pre-pass belongs to it), with split key ranges the merge (its largest dispatch),
     # and for fp32 inputs the fp32 kernel over the cache
     ps = "true" if a.teacher_psplit else "false"
     pats = [r"attn_combine_kernel<\d+, (true|false)>",
-            rf"attn_bf16_kernel<\d+, false, {ps}, (false|true), (false|true), (false|true), false, 0, "
-            r"(false|true)>",
+            rf"attn_bf16_kernel<\d+, false, {ps}, (false|true), (false|true), false, 0, (false|true)>",
             r"attn_f32_kernel<\d+, false, (false|true), false, false>"]
     def largest(k):
         f = max(fetch.get(k, [0.0])) * 1024.0 * sf
@@ -276,7 +274,7 @@ def main() -> None:
     full = [k for k in set(fetch) | set(write)
             if LIB_KERNEL.search(k) and any(re.fullmatch(pt, short(k)) for pt in pats)]
     if full:
-        print("\n## One full-cache attention launch (fast path, fixup and, where present, the merge)\n")
+        print("\n## One full-cache attention call (the kernel and, where present, the merge)\n")
         for k in sorted(full, key=short):
             print(f"- `{short(k)}`: {largest(k) / 1e6:,.1f} MB")
         print(f"\n    traffic_bytes_per_launch attend_full {sum(largest(k) for k in full):.0f}")
