@@ -32,6 +32,18 @@ def test_targets_tiles(M, din, dout, wdt):
     assert rel(host(T), ref) <= TOL
 
 
+# what the epilogue adds: a residual pair inside the matrix (16-byte loads), at its edges, and
+# with rows that are not a multiple of 16 bytes
+@pytest.mark.parametrize("M,d", [(31, 32), (256, 256), (300, 260), (260, 261), (1100, 1412)])
+def test_targets_residual(M, d):
+    print(f"targets with the residual, M={M} d={d}", flush=True)
+    Of, Oc = normal(1, M, d), normal(2, M, d)
+    W = normal(3, d, d, scale=d ** -0.5, dtype=torch.bfloat16)
+    T = pkv.compute_targets(Of, Oc, W, rho=1)
+    D = host(Of) - host(Oc)
+    assert rel(host(T), D @ host(W) + D) <= TOL
+
+
 # d_in around 128 and 192 multiples, and past the 128-tiles' limit (2,816)
 @pytest.mark.parametrize("rows,din,dout", [(1, 127, 3), (63, 129, 130), (200, 385, 384),
                                            (64, 2817, 33), (97, 2820, 128)])
