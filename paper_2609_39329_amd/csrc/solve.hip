@@ -922,8 +922,10 @@ __device__ __forceinline__ T unmask(U u) { return __builtin_bit_cast(T, u); }
 //     are exactly the values the lanes hold.
 // Bound by instruction issue (one wave, 4 cycles each): an fp32 leaf takes 2,240 cycles,
 // 3,780 on a sweep of one pivot per step.
-// A pivot that is not positive (or NaN) makes its reciprocal square root, and every later
-// pivot, NaN: the first such pivot is the failing column.
+// A pivot that is not positive, NaN or infinite makes its L_jj = t / sqrt(t) NaN, and the sum
+// of the leaf's L_jj tells (a good one is positive). The later pivots alone would not: past an
+// infinite pivot fp32's reciprocal square root is 0 and they stay finite and positive. The
+// first such pivot is the failing column.
 template <class T>
 __device__ __forceinline__ void leaf16(typename Acc4<T>::V a, T* Xo, int lane, int col0, int bs,
                                        int32_t* info, bool& failed) {
@@ -938,7 +940,7 @@ __device__ __forceinline__ void leaf16(typename Acc4<T>::V a, T* Xo, int lane, i
   typename Acc4<T>::V y;
 #pragma unroll
   for (int e = 0; e < 4; ++e) y[e] = acc_row<T>(g, e) == c ? T(1) : T(0);
-  T ljj[16];
+  T ljj[16], sum = T(0);
   static_for<4>([&](auto b_t) {
     constexpr int b = decltype(b_t)::value;
     // element (i, m) of D: fp32 in register m of lane (b, 4 b + i), fp64 in register b of (m, 4 b + i)
@@ -985,13 +987,13 @@ __device__ __forceinline__ void leaf16(typename Acc4<T>::V a, T* Xo, int lane, i
     const T x = times(y);
     if constexpr (b < 3) y = mfma16(-lp, x, y);
     Xo[(4 * b + g) * PT + c] = x;
-    // L_jj = t_j / sqrt(t_j): NaN from the first failing pivot on
     ljj[4 * b] = d(0, 0) * n00;
     ljj[4 * b + 1] = t11 * n11;
     ljj[4 * b + 2] = t22 * n22;
     ljj[4 * b + 3] = t33 * n33;
+    sum += (ljj[4 * b] + ljj[4 * b + 1]) + (ljj[4 * b + 2] + ljj[4 * b + 3]);
   });
-  if (__ballot(!(ljj[15] > T(0))) != 0 && !failed) {
+  if (__ballot(!(sum > T(0))) != 0 && !failed) {
     int bad = 15;
 #pragma unroll
     for (int j = 14; j >= 0; --j)

@@ -34,6 +34,24 @@ def test_first_failing_column(dtype, p, pivot):
     assert int(info.item()) == p + 1
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("p", [0, 1, 2, 3, 4, 7, 14, 15, 16, 30, 31, 63, 64, 127, 128, 131, 149])
+@pytest.mark.parametrize("later", [False, True])
+def test_infinite_pivot(dtype, p, later):
+    """One channel whose diagonal overflowed, its products with the others finite: the
+    reciprocal root of the pivot is 0, so the columns after it factor as if it were not there."""
+    print(f"infinite pivot {p} {dtype} later failure {later}", flush=True)
+    d = 150
+    rng = np.random.default_rng(p)
+    L = np.tril(rng.standard_normal((d, d)) * 0.05) + np.eye(d)
+    G = L @ L.T
+    G[p, p] = np.inf
+    if later and p + 3 < d:
+        G[p + 3, p + 3] = -5.0  # not reported
+    dW, info = pkv.solve_patch(torch.from_numpy(G).to(dtype).to(DEV), torch.ones((d, 4), dtype=dtype, device=DEV), 0.25)
+    assert int(info.item()) == p + 1
+
+
 @pytest.mark.parametrize("dtype,tol", [(torch.float32, 2e-5), (torch.float64, 1e-6)])
 @pytest.mark.parametrize("d", [1, 2, 3, 4, 5, 15, 16, 17, 33, 63, 64, 65, 100, 127, 128, 129, 145, 260])
 def test_block_remainders(dtype, tol, d):
