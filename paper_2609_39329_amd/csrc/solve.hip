@@ -1452,6 +1452,15 @@ SGemm to_sgemm(const GemmDesc<float>& g, bool& ak, bool& bj, int tile) {
   return s;
 }
 
+// 128 x 128 tiles of up to two problems
+int tiles128(const GemmDesc<float>* ds, int n) {
+  int t = 0;
+  bool a, b;
+  for (int i = 0; i < n; ++i)
+    if (ds[i].M > 0 && ds[i].N > 0 && ds[i].K > 0) t += to_sgemm(ds[i], a, b, S_BM).ntiles;
+  return t;
+}
+
 // fp32 products on three bf16 MFMA terms, up to two problems per launch. The
 // operand layouts the solve uses: A contiguous along k with B along k or j, or A
 // contiguous along i with B along j.
@@ -1461,14 +1470,10 @@ hipError_t run_group_split(const GemmDesc<float>* ds, int n, hipStream_t st) {
   bool ak[2] = {true, true}, bj[2] = {true, true};
   // K <= 128 everywhere (the factorisation's block-column updates) and too few 128 x 128
   // tiles to fill the CUs: the small-K kernel (latency rather than throughput)
-  int kmax = 0, tiles128 = 0;
+  int kmax = 0;
   for (int i = 0; i < n; ++i)
-    if (ds[i].M > 0 && ds[i].N > 0 && ds[i].K > 0) {
-      bool a, b;
-      kmax = std::max(kmax, ds[i].K);
-      tiles128 += to_sgemm(ds[i], a, b, S_BM).ntiles;
-    }
-  const bool small = kmax <= T_KMAX && tiles128 < 256;
+    if (ds[i].M > 0 && ds[i].N > 0 && ds[i].K > 0) kmax = std::max(kmax, ds[i].K);
+  const bool small = kmax <= T_KMAX && tiles128(ds, n) < 256;
   int m = 0;
   for (int i = 0; i < n; ++i)
     if (ds[i].M > 0 && ds[i].N > 0 && ds[i].K > 0) {
@@ -1509,7 +1514,14 @@ hipError_t run_group_split(const GemmDesc<float>* ds, int n, hipStream_t st) {
   return hipGetLastError();
 }
 
-// g[0], g[1] (an update by block column kb - NB) and the diagonal block at kb in one launch
+// g[0], g[1] (an update by block column kb - NB) and the diagonal block at kb in one launch, for
+// updates of fewer than kFuseTiles 128-tiles. Its 64-tiles take the longer the more there are
+// (128-tiles re-read the operands half as often), and from four rounds of 128-tiles on that
+// is more than the hidden factorisation: six-term solves with every update fused / in two
+// launches / by the rule, us: 1024 x 8192 463 / 530 / 463, x 24000 979 / 1002 / 977, x 32768
+// 1163 / 1144 / 1130, x 60000 2074 / 1890 / 1888; 4096 x 4096 2100 / 2320 / 2098, x 60000
+// 17521 / 16886 / 16880; 14336 x 14336 47490 / 47945 / 47482.
+constexpr int kFuseTiles = 1024;
 template <int TERMS>
 hipError_t run_update_potrf(const GemmDesc<float>* g, float* A, int64_t lda, int kb, int bs,
                             int32_t* info, const float* Lr, hipStream_t st) {
@@ -1637,7 +1649,7 @@ hipError_t solve_t(const T* G, const T* C, int64_t d64, int64_t dout64, double l
         g[1] = desc<T>(Lr, d, 1, Z + (int64_t)kb * dout, dout, 1, R + (int64_t)kb1 * dout, dout, wr,
                        dout, bs, mone, one);
         if constexpr (sizeof(T) == 4) {
-          if (products != kProductsExact) {
+          if (products != kProductsExact && tiles128(g, 2) < kFuseTiles) {
             const int bs1 = std::min(NB, d - kb1);
             PKV_TRY(products == kProductsSplit6
                         ? run_update_potrf<6>(g, A, d64, kb1, bs1, info, Lr, st)

@@ -3,7 +3,8 @@ steps, 16-wide leaves and blocks: the first failing column is reported exactly, 
 factorisation of well-posed systems of any block remainder matches numpy in fp64.
 
 Errors of a solve are bounded by a small multiple of cond * eps: cond below 50 here, so
-2e-5 in fp32 (2^-24 * 50 * 4) and 1e-6 after rounding fp64 results to fp32."""
+2e-5 in fp32 (2^-24 * 50 * 4), 2e-3 with three product terms (2^-16 a product) and 1e-6 after
+rounding fp64 results to fp32."""
 import numpy as np
 import pytest
 import torch
@@ -62,3 +63,18 @@ def test_block_remainders(dtype, tol, d):
     dW, info = pkv.solve_patch(torch.from_numpy(G).to(dtype).to(DEV), torch.from_numpy(C).to(dtype).to(DEV), 0.1)
     assert int(info.item()) == 0
     assert rel(host(dW), np.linalg.solve(G + 0.1 * np.eye(d), C)) <= tol
+
+
+@pytest.mark.parametrize("mode,tol", [(0, 2e-5), (32, 2e-3)])
+def test_wide_right_hand_side(mode, tol):
+    """Updates on both sides of the line between one launch with the next factorisation (the
+    second block column: 941 tiles of 128) and two (the first: 1413)."""
+    d, n = 400, 60000
+    print(f"solve {d} x {n} mode {mode}", flush=True)
+    rng = np.random.default_rng(7)
+    X = rng.standard_normal((4 * d, d)) / np.sqrt(4 * d)
+    G, C = X.T @ X, rng.standard_normal((d, n)).astype(np.float32)
+    dW, info = pkv.solve_patch(torch.from_numpy(G).float().to(DEV), torch.from_numpy(C).to(DEV), 0.1, mode=mode)
+    assert int(info.item()) == 0
+    cols = rng.choice(n, 200, replace=False)
+    assert rel(host(dW[:, torch.from_numpy(cols).to(DEV)]), np.linalg.solve(G + 0.1 * np.eye(d), C[:, cols].astype(np.float64))) <= tol
