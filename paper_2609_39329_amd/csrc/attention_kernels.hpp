@@ -1358,55 +1358,74 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(AttnParams p) 
   }
 }
 
-// Merge split-key partials: O = sum_s e^(m_s - m*) O_s / sum_s e^(m_s - m*) l_s.
-// One wave per row (n_split <= 64): lane s weighs split s, then the wave's 256 / DH lane
-// groups each sum every (256 / DH)-th split's O, four loads in flight, and the groups
-// are added in lane order. Bound by load latency: 64 ranges of 512 rows (head_dim 64) take
-// 4.5 us, 20 with one thread per 4 channels walking the ranges; 13 of 427 rows 3.9 (5.1).
-template <int DH, bool LOG2>
+// Merge split-key partials: O = sum_s e^(m_s - m*) O_s / sum_s e^(m_s - m*) l_s. LPR lanes
+// per row:
+//   a wave (n_split <= 64): lane s weighs split s, then the wave's 256 / DH lane groups each
+//     sum every (256 / DH)-th split's O, four loads in flight, and the groups are added in
+//     lane order;
+//   DH / 4 lanes, four channels each, walking the splits.
+// Bound by load latency while the rows are few, where the wave's shorter chain wins: 64 ranges
+// of 512 rows (head_dim 64) 4.1 us against 15.9, 16 of 4,096 4.1 against 5.6. From
+// kMergeRows rows on a wave per row is more waves than the chip holds (2 ranges of 32,768
+// rows: 13.4 against 4.8, head_dim 128 14.6 against 9.8; of 8,192 rows 4.9 against 4.1).
+constexpr int kMergeRows = 8192;
+template <int DH, bool LOG2, int LPR>
 __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restrict__ Opart,
                                                            const float* __restrict__ ML,
                                                            float* __restrict__ O, int rows,
                                                            int n_split, int Hkv, int G, int Hq) {
-  constexpr int C4 = DH / 4, NG = kWave / C4;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int64_t t = (int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
+  constexpr int C4 = DH / 4, NG = LPR / C4;
+  static_assert(LPR == kWave || LPR == C4, "a wave, or one lane group");
+  const int lane = threadIdx.x % LPR;
+  const int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPR;
   if (t >= (int64_t)Hkv * rows) return;
   const int r = (int)(t % rows);
   const int g = (int)(t / rows);
   const int64_t rid0 = (int64_t)g * n_split * rows + r;
-  const bool in = lane < n_split;
-  f32x2 ml = {-INFINITY, 0.f};
-  if (in) ml = *(const f32x2*)(ML + 2 * (rid0 + (int64_t)lane * rows));
-  float mx = ml[0];
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-  const float wgt = in ? (LOG2 ? exp2f(ml[0] - mx) : expf(ml[0] - mx)) : 0.f;
-  float l = wgt * ml[1];
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) l += __shfl_xor(l, o);
   const int c4 = lane % C4, sg = lane / C4;
   const f32x4* src = (const f32x4*)(Opart + rid0 * DH) + c4;
   const int64_t step = (int64_t)rows * C4;
   f32x4 acc = {};
-  for (int s0 = sg; s0 < n_split + sg; s0 += 4 * NG) {  // the same trip count on every lane
-    f32x4 v[4];
-    float wv[4];
+  float l = 0.f;
+  if constexpr (LPR == kWave) {
+    const bool in = lane < n_split;
+    f32x2 ml = {-INFINITY, 0.f};
+    if (in) ml = *(const f32x2*)(ML + 2 * (rid0 + (int64_t)lane * rows));
+    float mx = ml[0];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int s = s0 + u * NG;
-      v[u] = s < n_split ? src[s * step] : f32x4{};
-      wv[u] = __shfl(wgt, s & (kWave - 1));
-      if (s >= n_split) wv[u] = 0.f;
+    for (int o = kWave / 2; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    const float wgt = in ? (LOG2 ? exp2f(ml[0] - mx) : expf(ml[0] - mx)) : 0.f;
+    l = wgt * ml[1];
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) l += __shfl_xor(l, o);
+    for (int s0 = sg; s0 < n_split + sg; s0 += 4 * NG) {  // the same trip count on every lane
+      f32x4 v[4];
+      float wv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int s = s0 + u * NG;
+        v[u] = s < n_split ? src[s * step] : f32x4{};
+        wv[u] = __shfl(wgt, s & (kWave - 1));
+        if (s >= n_split) wv[u] = 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc += wv[u] * v[u];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) acc += wv[u] * v[u];
+    for (int o = C4; o < kWave; o <<= 1)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o);
+    if (sg != 0) return;
+  } else {
+    const float* ml = ML + 2 * rid0;
+    float mx = -INFINITY;
+    for (int s = 0; s < n_split; ++s) mx = fmaxf(mx, ml[2 * (int64_t)s * rows]);
+    for (int s = 0; s < n_split; ++s, ml += 2 * (int64_t)rows) {
+      const float wgt = LOG2 ? exp2f(ml[0] - mx) : expf(ml[0] - mx);
+      l += wgt * ml[1];
+      acc += wgt * src[s * step];
+    }
   }
-#pragma unroll
-  for (int o = C4; o < kWave; o <<= 1)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o);
-  if (sg != 0) return;
   const int m = r / G, j = r - m * G;
   *((f32x4*)(O + ((int64_t)m * Hq + g * G + j) * DH) + c4) = acc * (1.0f / l);
 }
@@ -1505,14 +1524,17 @@ hipError_t run_attention(const AttnShape& s, const AttnPlan& pl, AttnParams& p, 
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !part) return e;
-  const int64_t total = (int64_t)s.Hkv * p.rows;  // one wave per row
-  dim3 cg((unsigned)((total + 3) / 4));
-  if (s.bf16)
-    hipLaunchKernelGGL((attn_combine_kernel<DH, true>), cg, block, 0, st, p.Opart, p.ML, p.O,
-                       p.rows, pl.n_split, s.Hkv, p.G, s.Hq);
-  else
-    hipLaunchKernelGGL((attn_combine_kernel<DH, false>), cg, block, 0, st, p.Opart, p.ML, p.O,
-                       p.rows, pl.n_split, s.Hkv, p.G, s.Hq);
+  const int64_t total = (int64_t)s.Hkv * p.rows;
+  const bool wave = total < kMergeRows;
+  const dim3 cg((unsigned)((total * (wave ? kWave : DH / 4) + 255) / 256));
+#define PKV_LC(LOG2, LPR)                                                                            \
+  hipLaunchKernelGGL((attn_combine_kernel<DH, LOG2, LPR>), cg, block, 0, st, p.Opart, p.ML, p.O, p.rows, \
+                     pl.n_split, s.Hkv, p.G, s.Hq)
+  if (s.bf16 && wave) PKV_LC(true, kWave);
+  else if (s.bf16) PKV_LC(true, DH / 4);
+  else if (wave) PKV_LC(false, kWave);
+  else PKV_LC(false, DH / 4);
+#undef PKV_LC
   return hipGetLastError();
 }
 

@@ -264,7 +264,7 @@ def main() -> None:
     # teacher reads its contiguous cache's V as stored, so no V^T pre-pass belongs to it), with split key ranges the merge (its largest dispatch),
     # and for fp32 inputs the fp32 kernel over the cache
     ps = "true" if a.teacher_psplit else "false"
-    pats = [r"attn_combine_kernel<\d+, (true|false)>",
+    pats = [r"attn_combine_kernel<\d+, (true|false), \d+>",
             rf"attn_bf16_kernel<\d+, false, {ps}, (false|true), (false|true), false, 0, (false|true)>",
             r"attn_f32_kernel<\d+, false, (false|true), false, false>"]
     def largest(k):

@@ -66,3 +66,17 @@ def test_chunk_prefix_longer_than_the_cache():
         q, k, v, ks, vs = (host(t) for t in (Q, K, V, k_own, Vs))
         for h in range(4):
             assert rel(got[:, h], attend(q[:, h], k[0], v[0], (ks[0], vs[0]))) <= 5e-5, (gain, h)
+
+
+@pytest.mark.parametrize("M", [1023, 1024, 1025])
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("dtype,tol", [(torch.bfloat16, 5e-5), (torch.float32, 1e-5)])
+def test_merge_of_few_and_many_rows(M, dh, dtype, tol):
+    """Split key ranges merged by a wave per row below 8,192 rows (M * Hq), by lane groups
+    from there on. fp32: sums of 32 bits."""
+    print(f"merge M={M} dh={dh} {dtype}", flush=True)
+    Q, K, V = (normal(i, *s).to(dtype) for i, s in ((1, (M, 8, dh)), (2, (2, 900, dh)), (3, (2, 900, dh))))
+    got = host(pkv.attend_compressed(Q, K, V)).reshape(M, 8, dh)
+    q, k, v = (host(t) for t in (Q, K, V))
+    for h in range(8):
+        assert rel(got[:, h], attend(q[:, h], k[h // 4], v[h // 4])) <= tol, h
