@@ -230,8 +230,11 @@ __global__ __launch_bounds__(256) void vt_kernel(const void* __restrict__ V,
 // average: 222 -> 179 us; a 5,120-token chunk over 1,720 entries: 627 -> 570 us, both with the
 // steps past the last tile left out).
 //   kOrderRows (equal items): runs of row tiles of one head per XCD, as its L2 likes it.
-//   kOrderOwn (own entries): last key range and last row tiles first; a head's row tiles
-//     stay on its XCD (Hkv a multiple of 8) or are dealt to its XCDs (a divisor of 8).
+//   kOrderOwn (own entries): last key range and last row tiles first; a head's items
+//     stay on its XCD (Hkv a multiple of 8) or are dealt to its XCDs (a divisor of 8). All of
+//     its (range, row tile) pairs in one deal: with the row tiles of each range dealt anew, the
+//     first XCDs got up to one more item per range (1,600 queries of 8 / 2 heads over 16,000
+//     entries, 25 row tiles x 5 ranges: 35 items on an XCD of 32 CUs, 271 us; 204 now).
 //   kOrderCounts (per-head counts): heads by falling count, every head on every XCD.
 constexpr int kOrderRows = 0, kOrderOwn = 1, kOrderCounts = 2;
 struct WorkItem {
@@ -256,7 +259,7 @@ __host__ __device__ inline int order_per_xcd(int order, int heads, int row_tiles
   if (order == kOrderOwn && heads % kXcds == 0) return heads / kXcds * row_tiles * n_split;
   if (order == kOrderOwn && kXcds % heads == 0) {
     const int nx = kXcds / heads;
-    return (row_tiles + nx - 1) / nx * n_split;
+    return (row_tiles * n_split + nx - 1) / nx;
   }
   return per_xcd;
 }
@@ -283,10 +286,10 @@ __device__ __forceinline__ WorkItem work_item(const AttnParams& p) {
     return it;
   }
   if (OWN && p.order == kOrderOwn && kXcds % heads == 0) {
-    const int nx = kXcds / heads, nb = (p.row_tiles + nx - 1) / nx;
+    const int nx = kXcds / heads, q = i * nx + x % nx;
     it.g = x / nx;
-    it.split = p.n_split - 1 - i / nb;
-    it.rt = it.split < 0 ? -1 : p.row_tiles - 1 - (i % nb * nx + x % nx);
+    it.split = p.n_split - 1 - q / p.row_tiles;
+    it.rt = it.split < 0 ? -1 : p.row_tiles - 1 - q % p.row_tiles;
     return it;
   }
   const int slot = i * kXcds + x;

@@ -68,6 +68,23 @@ def test_chunk_prefix_longer_than_the_cache():
             assert rel(got[:, h], attend(q[:, h], k[0], v[0], (ks[0], vs[0]))) <= 5e-5, (gain, h)
 
 
+@pytest.mark.parametrize("Hq,Hkv,M,N", [(8, 2, 1600, 3000), (2, 1, 2500, 1500), (4, 4, 700, 2000),
+                                        (6, 3, 700, 2000), (4, 2, 270, 2600)])
+def test_ranges_times_row_tiles_not_a_multiple_of_the_xcds(Hq, Hkv, M, N):
+    """A chunk's (key range, row tile) pairs of a head dealt to its XCDs in one sequence that
+    ends inside a round, ranges chosen with the own prefix counted (equal or longer than the
+    cache's part)."""
+    print(f"deal Hq={Hq} Hkv={Hkv} M={M} N={N}", flush=True)
+    dh = 64
+    Q, K, V = normal(1, M, Hq, dh), normal(2, Hkv, N, dh), normal(3, Hkv, N, dh)
+    Ks, Vs = normal(4, Hkv, M, dh), normal(5, Hkv, M, dh)
+    got = host(pkv.attend_chunk(Q, K, V, Ks, Vs, p_terms=2)).reshape(M, Hq, dh)
+    q, k, v, ks, vs = (host(t) for t in (Q, K, V, Ks, Vs))
+    for h in range(Hq):
+        g = h // (Hq // Hkv)
+        assert rel(got[:, h], attend(q[:, h], k[g], v[g], (ks[g], vs[g]))) <= 5e-5, h
+
+
 @pytest.mark.parametrize("M", [1023, 1024, 1025])
 @pytest.mark.parametrize("dh", [64, 128])
 @pytest.mark.parametrize("dtype,tol", [(torch.bfloat16, 5e-5), (torch.float32, 1e-5)])
