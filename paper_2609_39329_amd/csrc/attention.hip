@@ -73,33 +73,45 @@ AttnPlan plan_attention(const AttnShape& s) {
   // (shared by the workgroups resident on the CU)
   const double tile_s = (double)kt * rows_wg * s.dh * 4.0 / (s.bf16 ? 4e12 / kWgPerCu : 0.45e12);
   // own entries (tiles of a row tile's causal prefix, longest and on average): work items
-  // of a short cache differ in length and are handed out longest first, which takes about
-  // the total over the CUs plus half of a shortest item; where the cache range is the
-  // longer part they run in rounds. That estimate chooses among the counts up to the one
-  // that rounds alone give (best_r): the workspace holds best_r ranges' partial results, so
-  // its size does not depend on the estimate.
+  // differ in length and are handed out longest first, so a call takes at least the longest
+  // item (the last range, which may be short, and the own tiles), the total over the CUs and,
+  // where the cache's part is the longer one, its rounds; where it is the shorter one about
+  // half of an item more than the total. All of these for every count: with the rounds alone
+  // in the second case, the own tiles of long key ranges cost nothing and too few ranges won.
+  // Us, that rule / this one / one that rounds alone give: 2,500 queries of 2 / 1 heads of 128
+  // over 5,000 entries 142 / 92 / 92, 700 of 6 / 3 over 2,000 65 / 48 / 48, 400 of 6 / 3 of 64
+  // over 5,000 29 / 27 / 33. (The partial results are read back by the merge; their writes
+  // pass under the longer items.)
+  // That estimate chooses among the counts up to the one that rounds alone give (best_r): the
+  // workspace holds best_r ranges' partial results, so its size does not depend on the
+  // estimate.
   const int64_t own_max = (s.Ms + kt - 1) / kt;
+  auto count = [&](int sp) {  // non-empty ranges of whole tiles
+    const int64_t tps = (ntiles + sp - 1) / sp;
+    return (int)((ntiles + tps - 1) / tps);
+  };
   auto ranges = [&](int limit, bool own) {
     double best = 1e300;
     int best_s = 1;
     for (int sp = 1; sp <= limit && sp <= ntiles; ++sp) {
       const int64_t tps = (ntiles + sp - 1) / sp;
-      const int64_t waves = (items * sp + (int64_t)slots - 1) / (int64_t)slots;
-      double cost = (double)waves * tps * tile_s;
-      if (own && tps < own_max)
-        cost = tile_s * std::max((double)items * (ntiles + 0.5 * own_max) / slots + 0.5 * tps,
-                                 (double)(tps + own_max));
-      if (sp > 1) cost += (double)s.Hkv * rows * (s.dh + 2) * 4.0 * sp * 2 / 4e12 + 4e-6;
+      const int n = own ? count(sp) : sp;
+      const int64_t waves = (items * n + (int64_t)slots - 1) / (int64_t)slots;
+      double tiles = (double)waves * tps;
+      if (own) {
+        const double total = (double)items * (ntiles + 0.5 * own_max) / slots;
+        const int64_t longest = std::max(tps, ntiles - (n - 1) * tps + own_max);
+        if (tps < own_max) tiles = total + 0.5 * tps;
+        tiles = std::max({tiles, total, (double)longest});
+      }
+      double cost = tiles * tile_s;
+      if (n > 1) cost += (double)s.Hkv * rows * (s.dh + 2) * 4.0 * n * (own ? 1 : 2) / 4e12 + 4e-6;
       if (cost < best * 0.98) {
         best = cost;
         best_s = sp;
       }
     }
     return best_s;
-  };
-  auto count = [&](int sp) {  // non-empty ranges of whole tiles
-    const int64_t tps = (ntiles + sp - 1) / sp;
-    return (int)((ntiles + tps - 1) / tps);
   };
   const int best_r = ranges(64, false);
   const int best_s = s.bf16 && own_max > 0 ? ranges(best_r, true) : best_r;
