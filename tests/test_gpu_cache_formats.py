@@ -56,6 +56,30 @@ def test_attend_cache_bias(dt, M, N, B, Hq, Hkv, dh):
     assert rel(O0, _ref(inp, K, V, inp.idx, None)) <= TOL[(dt, 2)]
 
 
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("B", [1, 31, 32, 33, 64, 65, 97, 128, 161, 700])
+def test_biased_gathered_tiles(B, dh):
+    """Indices loaded one step before their rows: entry counts around the 32-key tiles, and
+    keys outgrowing the first tile's scores (the rescaled pass, which starts over)."""
+    print(f"biased gathered B={B} dh={dh}", flush=True)
+    rng = np.random.default_rng(B + dh)
+    M, Hq, Hkv, N = 270, 4, 2, 900
+    q, k, v = (torch.from_numpy(rng.standard_normal(s)).bfloat16() for s in ((M, Hq, dh), (Hkv, N, dh), (Hkv, N, dh)))
+    idx = np.stack([rng.permutation(N)[:B] for _ in range(Hkv)]).astype(np.int32)
+    bias = rng.standard_normal((Hkv, B)).astype(np.float32)
+    for gain in (1.0, 14.0):
+        kk = k.clone()
+        for g in range(Hkv):
+            kk[g, idx[g, 2 * B // 3:]] *= gain
+        got = host(pkv.attend_cache(q.to(DEV), kk.to(DEV), v.to(DEV), idx=torch.from_numpy(idx).to(DEV),
+                                    bias=torch.from_numpy(bias).to(DEV))).reshape(M, Hq, dh)
+        for h in range(Hq):
+            g = h // (Hq // Hkv)
+            s = q[:, h].double().numpy() @ kk[g, idx[g]].double().numpy().T / np.sqrt(dh) + bias[g]
+            w = np.exp(s - s.max(1, keepdims=True))
+            assert rel(got[:, h], (w / w.sum(1, keepdims=True)) @ v[g, idx[g]].double().numpy()) <= 5e-5, (gain, h)
+
+
 @pytest.mark.parametrize("dt,bits", [("bf16", 8), ("bf16", 4), ("f32", 8), ("f32", 4)])
 def test_attend_cache_block_scaled(dt, bits):
     M, N, B, Hq, Hkv, dh = 96, 1200, 200, 8, 2, 128
