@@ -129,8 +129,9 @@ AttnPlan plan_attention(const AttnShape& s) {
     pl.ws_bytes += align_up((size_t)s.Hkv * ntiles * 32 * s.dh * 2);  // V^T tiles
     if (s.Ms > 0)  // V^T tiles of the own entries
       pl.ws_bytes += align_up((size_t)s.Hkv * ((s.Ms + kKeyTile - 1) / kKeyTile) * 32 * s.dh * 2);
-    // one word per work item, unused: the size of the interface, which buffers of callers
-    // and the limit of the fixed scratch follow
+    // one word per work item, the first of which hold the heads' order (launch_attention):
+    // the size of the interface, which buffers of callers and the limit of the fixed scratch
+    // follow
     pl.ws_bytes += align_up((size_t)items * n_ws * sizeof(int));
   }
   return pl;
@@ -175,6 +176,9 @@ hipError_t launch_attention(const AttnShape& s, const void* Q, const void* K, co
       p.Vts = (const __bf16*)((char*)ws + off);
       p.own_tiles = (int)((s.Ms + kKeyTile - 1) / kKeyTile);
     }
+    // then the heads' order (at most 64 words)
+    off += align_up((size_t)s.Hkv * (s.Ms > 0 ? p.own_tiles : vt_tiles) * 32 * s.dh * 2);
+    p.head_order = (const int32_t*)((char*)ws + off);
   }
   p.Hq = s.Hq;
   p.G = s.Hq / s.Hkv;

@@ -86,6 +86,7 @@ struct AttnParams {
   int row_tiles;
   int total_items, per_xcd;
   int order;  // bf16 path: how workgroups map to work items (kOrder..., see work_item)
+  const int32_t* head_order;  // kOrderCounts: see order_heads
   float c;  // bf16: scale * log2(e); f32: scale
   // own entries of a reference chunk (OWN kernels): Ks, Vs [Hkv][Ms][dh]; Vts their
   // V^T tiles (bf16)
@@ -161,6 +162,52 @@ __device__ __forceinline__ bf16x8 mx_expand8(uint32_t w0, uint32_t w1, int ex) {
   return v;
 }
 
+// Work items of unequal length (a chunk's own prefix grows with the row tile; per-head index
+// sets differ between heads) are handed out longest first, each XCD the same mix, so the
+// CUs finish together: the hardware takes workgroups in order, workgroup b on XCD b % 8.
+// With items in row order and a head per XCD, the last items were the longest and the
+// XCD of the longest head finished last (4,096 queries, 8 heads of 1,720 entries on
+// average: 222 -> 179 us; a 5,120-token chunk over 1,720 entries: 627 -> 570 us, both with the
+// steps past the last tile left out).
+//   kOrderRows (equal items): runs of row tiles of one head per XCD, as its L2 likes it.
+//   kOrderOwn (own entries): last key range and last row tiles first; a head's items
+//     stay on its XCD (Hkv a multiple of 8) or are dealt to its XCDs (a divisor of 8). All of
+//     its (range, row tile) pairs in one deal: with the row tiles of each range dealt anew, the
+//     first XCDs got up to one more item per range (1,600 queries of 8 / 2 heads over 16,000
+//     entries, 25 row tiles x 5 ranges: 35 items on an XCD of 32 CUs, 271 us; 204 now).
+//   kOrderCounts (per-head counts): heads by falling count, every head on every XCD, unless
+//     runs of heads are balanced (order_heads).
+constexpr int kOrderRows = 0, kOrderOwn = 1, kOrderCounts = 2;
+struct WorkItem {
+  int g, split, rt;  // KV head, key range, row tile (rt < 0: none)
+};
+
+// kOrderCounts, one wave (heads <= 64): out[k] = the head of rank k by falling count (ties:
+// lower head first), plus kRuns if runs of heads in order load the XCDs alike, the fullest
+// one at most kBalanced of the mean. Such runs share their L2 and are the better order where
+// the items are more than one round or a head has one range, its row tiles reading the same
+// keys at the same time (4,096 queries of 32 heads of 64 over 300 entries each: 38 us dealt
+// over all XCDs, 35 as runs; 1,500 over 1,000 38 and 36); in one round of several ranges the
+// deal is (512 of 8 / 2 heads of 128 over 3,000: 33 us, 36 as runs).
+constexpr float kBalanced = 1.05f;
+constexpr int kRuns = 256;
+__device__ __forceinline__ void order_heads(const int32_t* counts, int heads, int Nk, int32_t* out) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int mine = lane < heads ? min(max(counts[lane], 1), Nk) : 0;
+  // in eighths of a head: head h is [8 h, 8 h + 8), XCD x takes [x heads, (x + 1) heads)
+  const int lo = lane % kXcds * heads, hi = lo + heads;
+  int rank = 0;
+  float load = 0.f, mean = 0.f;
+  for (int h = 0; h < heads; ++h) {
+    const int c = __builtin_amdgcn_readlane(mine, h);
+    rank += (c > mine || (c == mine && h < lane)) ? 1 : 0;
+    mean += (float)c;
+    load += (float)c * (float)max(0, min((h + 1) * kXcds, hi) - max(h * kXcds, lo));
+  }
+  const bool runs = __ballot(load > kBalanced * mean) == 0;
+  if (lane < heads) out[rank] = lane + (runs ? kRuns : 0);
+}
+
 // V -> V^T in 32-key tiles, so that the P V product reads V with plain 16-byte LDS
 // reads: Vt[g][tile][d][pos] (bf16). Within a tile the keys are stored in the
 // k-slot order of the P fragments: key 16b + r (r < 16) sits at position
@@ -168,18 +215,21 @@ __device__ __forceinline__ bf16x8 mx_expand8(uint32_t w0, uint32_t w1, int ex) {
 // (keys 16b + 4h + {0..3} and 16b + 8 + 4h + {0..3}) are 8 consecutive positions.
 // Keys at or past the head's entry count (and gathered rows outside the cache) are
 // zero. GATHER: key n of head g is row idx[g * idx_stride + n] of V. KQ = 8 or 4: V
-// holds block-scaled integers (exponents in Ve), expanded to bf16 on the way.
+// holds block-scaled integers (exponents in Ve), expanded to bf16 on the way. head_order (or
+// null): the first workgroup orders the heads for the attention kernel (order_heads).
 template <int DH, bool GATHER, int KQ>
 __global__ __launch_bounds__(256) void vt_kernel(const void* __restrict__ V,
                                                  const int8_t* __restrict__ Ve,
                                                  const int32_t* __restrict__ idx, int idx_stride,
                                                  const int32_t* __restrict__ counts,
                                                  int64_t src_rows, int Nk, int ntiles,
-                                                 __bf16* __restrict__ Vt) {
+                                                 __bf16* __restrict__ Vt,
+                                                 int32_t* __restrict__ head_order) {
   constexpr int CH = DH / 8;     // 16-byte chunks per V row
   constexpr int SP = DH + 2;     // LDS pitch (elements) of the [key][d] staging tile
   __shared__ __bf16 sm[32 * SP];
   const int tile = blockIdx.x, g = blockIdx.y, tid = threadIdx.x;
+  if (head_order && tile == 0 && g == 0 && tid < kWave) order_heads(counts, gridDim.y, Nk, head_order);
   constexpr int RB = DH * (KQ ? KQ : 16) / 8;  // bytes of one stored V row
   const char* Vg = (const char*)V + (int64_t)g * src_rows * RB;
   const int nk = counts ? min(max(counts[g], 1), Nk) : Nk;
@@ -222,53 +272,14 @@ __global__ __launch_bounds__(256) void vt_kernel(const void* __restrict__ V,
   }
 }
 
-// Work items of unequal length (a chunk's own prefix grows with the row tile; per-head index
-// sets differ between heads) are handed out longest first, each XCD the same mix, so the
-// CUs finish together: the hardware takes workgroups in order, workgroup b on XCD b % 8.
-// With items in row order and a head per XCD, the last items were the longest and the
-// XCD of the longest head finished last (4,096 queries, 8 heads of 1,720 entries on
-// average: 222 -> 179 us; a 5,120-token chunk over 1,720 entries: 627 -> 570 us, both with the
-// steps past the last tile left out).
-//   kOrderRows (equal items): runs of row tiles of one head per XCD, as its L2 likes it.
-//   kOrderOwn (own entries): last key range and last row tiles first; a head's items
-//     stay on its XCD (Hkv a multiple of 8) or are dealt to its XCDs (a divisor of 8). All of
-//     its (range, row tile) pairs in one deal: with the row tiles of each range dealt anew, the
-//     first XCDs got up to one more item per range (1,600 queries of 8 / 2 heads over 16,000
-//     entries, 25 row tiles x 5 ranges: 35 items on an XCD of 32 CUs, 271 us; 204 now).
-//   kOrderCounts (per-head counts): heads by falling count, every head on every XCD.
-constexpr int kOrderRows = 0, kOrderOwn = 1, kOrderCounts = 2;
-struct WorkItem {
-  int g, split, rt;  // KV head, key range, row tile (rt < 0: none)
-};
-
-// the head of rank k by falling count (ties: lower head first); heads <= 64, whole wave
-__device__ __forceinline__ int head_of_rank(const int32_t* counts, int heads, int Nk, int k) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int mine = lane < heads ? min(max(counts[lane], 1), Nk) : 0;
-  int rank = 0;
-  for (int h = 0; h < heads; ++h) {
-    const int c = __builtin_amdgcn_readlane(mine, h);
-    rank += (c > mine || (c == mine && h < lane)) ? 1 : 0;
-  }
-  const uint64_t hit = __ballot(lane < heads && rank == k);
-  return (int)__builtin_ctzll(hit);
-}
-
-// workgroups per XCD
-__host__ __device__ inline int order_per_xcd(int order, int heads, int row_tiles, int n_split, int per_xcd) {
-  if (order == kOrderOwn && heads % kXcds == 0) return heads / kXcds * row_tiles * n_split;
-  if (order == kOrderOwn && kXcds % heads == 0) {
-    const int nx = kXcds / heads;
-    return (row_tiles * n_split + nx - 1) / nx;
-  }
-  return per_xcd;
-}
-
 template <bool OWN>
 __device__ __forceinline__ WorkItem work_item(const AttnParams& p) {
   const int heads = p.Hq / p.G, x = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
   WorkItem it{0, 0, -1};
-  if (p.order == kOrderRows) {
+  int order = p.order;
+  if (order == kOrderCounts && (p.total_items > 256 * kWgPerCu || p.n_split == 1) && p.head_order[0] >= kRuns)
+    order = OWN ? kOrderOwn : kOrderRows;
+  if (order == kOrderRows) {
     const int w = x * p.per_xcd + i;
     if (w < p.total_items) {
       it.rt = w % p.row_tiles;
@@ -278,14 +289,14 @@ __device__ __forceinline__ WorkItem work_item(const AttnParams& p) {
     }
     return it;
   }
-  if (OWN && p.order == kOrderOwn && heads % kXcds == 0) {
+  if (OWN && order == kOrderOwn && heads % kXcds == 0) {
     const int hx = heads / kXcds, q = i / hx;
     it.g = x * hx + i % hx;
     it.split = p.n_split - 1 - q / p.row_tiles;
     it.rt = it.split < 0 ? -1 : p.row_tiles - 1 - q % p.row_tiles;
     return it;
   }
-  if (OWN && p.order == kOrderOwn && kXcds % heads == 0) {
+  if (OWN && order == kOrderOwn && kXcds % heads == 0) {
     const int nx = kXcds / heads, q = i * nx + x % nx;
     it.g = x / nx;
     it.split = p.n_split - 1 - q / p.row_tiles;
@@ -306,7 +317,7 @@ __device__ __forceinline__ WorkItem work_item(const AttnParams& p) {
     rank = q % heads;
     it.split = q / heads;
   }
-  it.g = p.order == kOrderCounts ? head_of_rank(p.counts, heads, p.Nk, rank) : rank;
+  it.g = order == kOrderCounts ? p.head_order[rank] % kRuns : rank;
   return it;
 }
 
@@ -1480,19 +1491,19 @@ hipError_t run_attention(const AttnShape& s, const AttnPlan& pl, AttnParams& p, 
   dim3 grid(pl.grid), block(256);
   if (s.bf16) {
     p.order = p.counts && s.Hkv <= kWave ? kOrderCounts : own ? kOrderOwn : kOrderRows;
-    grid = dim3(order_per_xcd(p.order, s.Hkv, pl.row_tiles, pl.n_split, pl.per_xcd) * kXcds);
+    int32_t* ho = p.order == kOrderCounts ? const_cast<int32_t*>(p.head_order) : nullptr;
     const dim3 vg((unsigned)p.vt_tiles, (unsigned)s.Hkv);
     if (gather)
       hipLaunchKernelGGL((vt_kernel<DH, true, KQ>), vg, block, 0, st, p.V, p.Ve, p.idx,
-                         p.idx_stride, p.counts, p.src_rows, p.Nk, p.vt_tiles, (__bf16*)p.Vt);
+                         p.idx_stride, p.counts, p.src_rows, p.Nk, p.vt_tiles, (__bf16*)p.Vt, ho);
     else if (!vnat)
       hipLaunchKernelGGL((vt_kernel<DH, false, KQ>), vg, block, 0, st, p.V, p.Ve, p.idx,
-                         p.idx_stride, p.counts, p.src_rows, p.Nk, p.vt_tiles, (__bf16*)p.Vt);
+                         p.idx_stride, p.counts, p.src_rows, p.Nk, p.vt_tiles, (__bf16*)p.Vt, ho);
     if constexpr (KQ == 0) {
       if (own && !vnat) {  // V^T tiles of the chunk's own entries
         const dim3 og((unsigned)p.own_tiles, (unsigned)s.Hkv);
         hipLaunchKernelGGL((vt_kernel<DH, false, 0>), og, block, 0, st, p.Vs, nullptr, nullptr, 0,
-                           nullptr, (int64_t)p.Ms, p.Ms, p.own_tiles, (__bf16*)p.Vts);
+                           nullptr, (int64_t)p.Ms, p.Ms, p.own_tiles, (__bf16*)p.Vts, nullptr);
       }
     }
     hipError_t e = hipGetLastError();
