@@ -321,11 +321,13 @@ __device__ __forceinline__ WorkItem work_item(const AttnParams& p) {
   return it;
 }
 
-// Waves per SIMD that the registers must allow: at head_dim 64 the plain one-term variants fit
-// two workgroups per CU while they keep to 128 registers (130 without the bound: 40,000
-// queries of 8 heads over 4,096 keys 342 us, 323 with it).
-constexpr int waves_per_simd(int dh, bool gather, bool psplit, bool own, bool bias, int kq) {
-  return dh == 64 && !gather && !psplit && !own && !bias && kq == 0 ? 4 : kWgPerCu;
+// Waves per SIMD that the registers must allow: at head_dim 64 the plain variants fit two
+// workgroups per CU while they keep to 128 registers (one-term P 130 without the bound: 40,000
+// queries of 8 heads over 4,096 keys 342 us, 323 with it; two-term P 132, with the bound up to
+// 3 registers in scratch memory: 1,500 queries of 16 / 16 heads over 40,000 keys 397 us and 366,
+// 4,096 of 28 / 4 over 10,000 497 and 460).
+constexpr int waves_per_simd(int dh, bool gather, bool own, bool bias, int kq) {
+  return dh == 64 && !gather && !own && !bias && kq == 0 ? 4 : kWgPerCu;
 }
 
 // Fast path: each row's exponent offset is fixed to the exact max of
@@ -343,7 +345,7 @@ constexpr int waves_per_simd(int dh, bool gather, bool psplit, bool own, bool bi
 // no V^T tiles; V tiles arrive in their stored [key][d] order and the P V product reads
 // its V operand with transposing LDS reads (see vfrag).
 template <int DH, bool GATHER, bool PSPLIT, bool PARTIAL, bool OWN, bool BIAS, int KQ, bool VNAT>
-__global__ __launch_bounds__(kThreadsBf16, waves_per_simd(DH, GATHER, PSPLIT, OWN, BIAS, KQ))
+__global__ __launch_bounds__(kThreadsBf16, waves_per_simd(DH, GATHER, OWN, BIAS, KQ))
     void attn_bf16_kernel(AttnParams p) {
   static_assert(!(OWN && BIAS), "own entries carry no bias");
   static_assert(KQ == 0 || KQ == 8 || KQ == 4, "bf16, int8 or int4 keys");
