@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
 @pytest.mark.parametrize("p", [0, 1, 2, 3, 4, 7, 15, 16, 18, 63, 64, 65, 126, 127, 128, 131, 149])
-@pytest.mark.parametrize("pivot", [-1.0, 0.0, float("nan")])
+@pytest.mark.parametrize("pivot", [-1.0, -1e-3, float("nan")])
 def test_first_failing_column(dtype, p, pivot):
     print(f"failing column {p} pivot {pivot} {dtype}", flush=True)
     d = 150
@@ -27,10 +27,28 @@ def test_first_failing_column(dtype, p, pivot):
     s = L[p, :p] @ L[p, :p]
     lam = 0.25
     G -= lam * np.eye(d)
-    G[p, p] = s + (pivot if pivot != 0.0 else -1e-3) - lam  # Schur complement of column p
+    G[p, p] = s + pivot - lam  # Schur complement of column p
     G[p + 1:, p + 1:] += 2 * np.eye(d - p - 1)
     if p + 3 < d:
         G[p + 3, p + 3] = -5.0  # a later failure is not reported
+    dW, info = pkv.solve_patch(torch.from_numpy(G).to(dtype).to(DEV), torch.ones((d, 4), dtype=dtype, device=DEV), lam)
+    assert int(info.item()) == p + 1
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("p", [0, 1, 2, 3, 4, 7, 15, 16, 18, 63, 64, 65, 126, 127, 128, 131, 149])
+@pytest.mark.parametrize("coupled", [False, True])
+def test_zero_pivot(dtype, p, coupled):
+    """A Schur complement of exactly zero: every other pivot is 1 and the entries are small
+    whole numbers, so each product and sum of the factorisation is exact."""
+    print(f"zero pivot {p} {dtype} coupled {coupled}", flush=True)
+    d, lam = 150, 0.25
+    L = np.eye(d)
+    L[p, p] = 0.0
+    if coupled:
+        L[p, :p:3] = 1.0   # row p on columns before it: G[p, p] + lam is their number
+        L[p + 1:, :p:7] = -1.0
+    G = L @ L.T - lam * np.eye(d)
     dW, info = pkv.solve_patch(torch.from_numpy(G).to(dtype).to(DEV), torch.ones((d, 4), dtype=dtype, device=DEV), lam)
     assert int(info.item()) == p + 1
 
