@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(const __bf16* __res
 // 192-tile reaches past a 256-padded plane) read as zeros through the buffer range.
 struct BGemm {
   const __bf16* A[2];  // planes of A [Ip][Kp]
-  const __bf16* B[2];  // planes of B [Jp][Kp]; BNAT: the bf16 matrix itself, [K][ldb] (SWIGLU: gate, up)
+  const __bf16* B[2];  // planes of B [Jp][Kp]; BNAT: the bf16 gate and up matrices, [K][ldb]
   int64_t ld;          // Kp
   int64_t ldb;         // BNAT: row length of B
   int K;               // BNAT: rows of B
@@ -240,7 +240,7 @@ using BgSym = BgCfg<192, 192, 96, 96, 3, 2>;
 
 template <class CFG, int NA, int NB, int NT, int TA, int TB, bool SYM, bool BNAT, bool SWIGLU>
 __global__ __launch_bounds__(CFG::NTH, 1) void bgemm_kernel(BGemm p) {
-  static_assert(!BNAT || (NB == 1 && CFG::KSP == 1 && !SYM && CFG::NTH == 512), "one plane of B as stored");
+  static_assert(!BNAT || (SWIGLU && NB == 1 && CFG::KSP == 1 && CFG::NTH == 512), "gate and up as stored");
   static_assert(!SWIGLU || (!SYM && (CFG::WN / 32) % 2 == 0), "gate and up blocks side by side");
   constexpr int TI = CFG::TI, TJ = CFG::TJ, WM = CFG::WM, WN = CFG::WN, S = CFG::S;
   constexpr int KSP = CFG::KSP, NTH = CFG::NTH;
@@ -328,18 +328,18 @@ __global__ __launch_bounds__(CFG::NTH, 1) void bgemm_kernel(BGemm p) {
   const uint32_t voff0 = (uint32_t)(((lt / 4) * p.ld + (((lt % 4) ^ ((lt / 16) % 4)) * 8)) * 2);
   // BNAT: B's chunk as stored, in sub-tiles [TJ / 32][32 k][32 columns] of 64-byte rows:
   // 16-byte chunk c of the stage's B part holds k (c / 4) % 32, columns 8 (c % 4) .. of
-  // sub-tile c / 128. With SWIGLU the sub-tiles alternate between gate and up (a wave's 64
-  // chunks lie in one sub-tile of fixed parity). Rows past K read as zeros through the
+  // sub-tile c / 128. The sub-tiles alternate between gate and up (a wave's 64 chunks lie in
+  // one sub-tile of fixed parity). Rows past K read as zeros through the
   // buffer range (the row offset is in the lane's offset: the range check leaves the scalar
   // offset out); columns past ldb run into the next row and are never stored.
-  const int bw = SWIGLU ? (__builtin_amdgcn_readfirstlane(wid) >> 1) & 1 : 0;
-  const int jcol = SWIGLU ? j0 / 2 : j0;  // first column of this tile in the stored matrix
+  const int bw = BNAT ? (__builtin_amdgcn_readfirstlane(wid) >> 1) & 1 : 0;
+  const int jcol = j0 / 2;  // first column of this tile in the stored matrices
   const __bf16* bn = p.B[bw] + jcol;
   const uint32_t bn_bytes = BNAT ? (uint32_t)(((int64_t)p.K * p.ldb - jcol) * 2) : 0;
   const __amdgpu_buffer_rsrc_t rsb =
       __builtin_amdgcn_make_buffer_rsrc((void*)bn, 0, bn_bytes, 0x00020000);
   const uint32_t voffb =
-      (uint32_t)(((tid >> 2) & 31) * p.ldb + (SWIGLU ? tid >> 8 : tid >> 7) * 32 + (tid & 3) * 8) * 2;
+      (uint32_t)(((tid >> 2) & 31) * p.ldb + (tid >> 8) * 32 + (tid & 3) * 8) * 2;
   auto issue = [&](int q, int buf) {
     const uint32_t k0b = (uint32_t)(q * BG_KC * 2);
     static_for<LPT>([&](auto u_t) {
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(CFG::NTH, 1) void bgemm_kernel(BGemm p) {
       const uint32_t vo = voff0 + (uint32_t)(ur * RPU * p.ld * 2);
       if constexpr (BNAT && !in_a) {
         PKV_LDS void* dst = (PKV_LDS void*)&lds[buf][(u * NTH + wid * 64) * 8];
-        const uint32_t vb = voffb + (uint32_t)((u - NA * PPA) * (SWIGLU ? 2 : 4) * 64) +
+        const uint32_t vb = voffb + (uint32_t)((u - NA * PPA) * 2 * 64) +
                             (uint32_t)(q * BG_KC) * (uint32_t)(p.ldb * 2);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsb, dst, 16, vb, 0, 0, 0);
       } else if constexpr (KSP == 1) {
@@ -637,8 +637,12 @@ hipError_t launch_bgemm(BGemm& p, hipStream_t st) {
 
 // The tile whose rounds over the 256 CUs are estimated shortest: 1, 0.62 and 0.42 are the
 // measured times of one round of 256 x 256, 128 x 256 and 128 x 128 tiles. Targets of
-// d = 4096 with all three (us): M = 1024 223 / 138 / 110, 2048 241 / 173 / 199, 3000
-// 260 / 283 / 282, 4096 323 / 339 / 383; d = 1500, M = 2000 135 / 80 / 56. Symmetric
+// d = 4096 with all three (us): M = 1024 179 / 114 / 93, 2048 192 / 147 / 172, 3000
+// 222 / 243 / 244, 4096 277 / 289 / 330. The same line suits more terms: fp32 weights (three)
+// M = 1024 263 / 164 / 127, 2048 279 / 209 / 231, 4096 381 / 408 / 442, d = 1500, M = 2000
+// 129 / 78 / 56; SwiGLU features of fp32 weights 4096 x 14336, M = 4096 2302 / 2560 / 2991; whole
+// dual patches (X^T Y of four) of 512 rows, 1024 x 4096 277 / 261 / 251, of 4096, 14336 x 4096
+// 4473 / 4482 / 4670 (4449 with the rest of the rounds on its own shape). Symmetric
 // products: 128-tiles while one round of them holds the triangle (d = 1500, M = 2000, G and C:
 // 222 us on large tiles, 100 now), else 192-tiles.
 template <int NA, int NB, int NT, int TA, int TB, bool SYM, bool BNAT = false, bool SWIGLU = false>
