@@ -419,10 +419,9 @@ def main():
                                  "patchkv_attend_cache (full cache, two-term P: 1.5x the MFMA "
                                  "work of the algorithmic flops counted here)"
                                  if cfg.teacher_p_terms == 2 else "patchkv_attend_full")
-                                + ((": vt_kernel (V^T tiles of the cache and own entries) + "
-                                    "attn_bf16_kernel" if chunked else
-                                    ": attn_bf16_kernel (V tiles as stored)")
-                                   if cfg.dtype == "bf16" else ": attn_f32_kernel")),
+                                + (": attn_bf16_kernel (V tiles as stored)"
+                                   if cfg.dtype == "bf16" else ": attn_f32_kernel")
+                                + " + the merge where keys are split"),
                      "flops_per_launch": att_flops_full,
                      "traffic_unit": "HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
                      "traffic_source": os.path.relpath(traffic_profile(cfg), ROOT) if traffic else None,

@@ -11,8 +11,8 @@ Three modes (each prints one summary with the command it summarises):
                traffic_bytes_per_launch attend_full <bytes>
                source_sha256 <file> <hash>
            are what bench.py reads back (it trusts the figure only while the hashed
-           sources are unchanged): the V^T pre-pass, fast path and fixup of one
-           full-cache attention.
+           sources are unchanged): the kernel and the merge, if any, of one full-cache
+           attention.
   trace    kernel time per kernel from a ``--kernel-trace --stats`` folder.
   mfma     ``--pmc MfmaUtil MfmaFlopsBF16 --kernel-trace`` folder: MFMA busy share and
            executed bf16 MFMA work per kernel.
@@ -261,8 +261,9 @@ def main() -> None:
 
     # the full-cache pass: the teacher's kernel (one dispatch per layer or reference chunk:
     # no other call uses this instantiation; a chunk's pass carries its own entries; the
-    # teacher reads its contiguous cache's V as stored, so no V^T pre-pass belongs to it), with split key ranges the merge (its largest dispatch),
-    # and for fp32 inputs the fp32 kernel over the cache
+    # teacher reads its contiguous cache's V as stored, so no V^T pre-pass belongs to it),
+    # with split key ranges the merge (its largest dispatch), and for fp32 inputs the fp32
+    # kernel over the cache
     ps = "true" if a.teacher_psplit else "false"
     pats = [r"attn_combine_kernel<\d+, (true|false), \d+>",
             rf"attn_bf16_kernel<\d+, false, {ps}, (false|true), (false|true), false, 0, (false|true)>",
