@@ -177,7 +177,11 @@ __device__ __forceinline__ bf16x8 mx_expand8(uint32_t w0, uint32_t w1, int ex) {
 //     entries, 25 row tiles x 5 ranges: 35 items on an XCD of 32 CUs, 271 us; 204 now).
 //   kOrderCounts (per-head counts): heads by falling count, every head on every XCD, unless
 //     runs of heads are balanced (order_heads).
-constexpr int kOrderRows = 0, kOrderOwn = 1, kOrderCounts = 2;
+//   kOrderDeal (per-head counts, one round of several ranges): every head on every XCD, in
+//     order: all items start at once, so no rank is waited for (the smallest serving call
+//     of the benchmark's cases 22.6 us with each workgroup ranking the heads, one more ranked by the
+//     pre-pass, 21.6 now).
+constexpr int kOrderRows = 0, kOrderOwn = 1, kOrderCounts = 2, kOrderDeal = 3;
 struct WorkItem {
   int g, split, rt;  // KV head, key range, row tile (rt < 0: none)
 };
@@ -277,8 +281,7 @@ __device__ __forceinline__ WorkItem work_item(const AttnParams& p) {
   const int heads = p.Hq / p.G, x = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
   WorkItem it{0, 0, -1};
   int order = p.order;
-  if (order == kOrderCounts && (p.total_items > 256 * kWgPerCu || p.n_split == 1) && p.head_order[0] >= kRuns)
-    order = OWN ? kOrderOwn : kOrderRows;
+  if (order == kOrderCounts && p.head_order[0] >= kRuns) order = OWN ? kOrderOwn : kOrderRows;
   if (order == kOrderRows) {
     const int w = x * p.per_xcd + i;
     if (w < p.total_items) {
@@ -1492,7 +1495,8 @@ hipError_t run_attention(const AttnShape& s, const AttnPlan& pl, AttnParams& p, 
   const bool vnat = KQ == 0 && s.bf16 && !gather && !bias && !p.counts && p.src_rows == p.Nk;
   dim3 grid(pl.grid), block(256);
   if (s.bf16) {
-    p.order = p.counts && s.Hkv <= kWave ? kOrderCounts : own ? kOrderOwn : kOrderRows;
+    const bool ranked = pl.total_items > 256 * kWgPerCu || !part;
+    p.order = p.counts && s.Hkv <= kWave ? (ranked ? kOrderCounts : kOrderDeal) : own ? kOrderOwn : kOrderRows;
     int32_t* ho = p.order == kOrderCounts ? const_cast<int32_t*>(p.head_order) : nullptr;
     const dim3 vg((unsigned)p.vt_tiles, (unsigned)s.Hkv);
     if (gather)
