@@ -81,7 +81,9 @@ AttnPlan plan_attention(const AttnShape& s) {
   // Us, that rule / this one / one that rounds alone give: 2,500 queries of 2 / 1 heads of 128
   // over 5,000 entries 142 / 92 / 92, 700 of 6 / 3 over 2,000 65 / 48 / 48, 400 of 6 / 3 of 64
   // over 5,000 29 / 27 / 33. (The partial results are read back by the merge; their writes
-  // pass under the longer items.)
+  // pass under the longer items. A split costs 8 us besides: the merge's launch, and ranges of a few
+  // tiles take as long as their prologue: 100 queries of 4 / 4 heads of 64 over 300 entries 23.4 us
+  // on one range, 26.6 on ten.)
   // That estimate chooses among the counts up to the one that rounds alone give (best_r): the
   // workspace holds best_r ranges' partial results, so its size does not depend on the
   // estimate.
@@ -105,7 +107,7 @@ AttnPlan plan_attention(const AttnShape& s) {
         tiles = std::max({tiles, total, (double)longest});
       }
       double cost = tiles * tile_s;
-      if (n > 1) cost += (double)s.Hkv * rows * (s.dh + 2) * 4.0 * n * (own ? 1 : 2) / 4e12 + 4e-6;
+      if (n > 1) cost += (double)s.Hkv * rows * (s.dh + 2) * 4.0 * n * (own ? 1 : 2) / 4e12 + (own ? 8e-6 : 4e-6);
       if (cost < best * 0.98) {
         best = cost;
         best_s = sp;
