@@ -54,6 +54,37 @@ def test_every_item_once(Hq, Hkv, M, counts, own):
         assert rel(got[:, h], ref) <= 5e-5, h
 
 
+@pytest.mark.parametrize("Hq,Hkv,M,B", [(16, 16, 300, 20), (6, 3, 300, 30), (5, 1, 170, 9), (12, 12, 270, 25),
+                                        (65, 65, 40, 20), (64, 64, 1100, 90)])
+@pytest.mark.parametrize("counts", ["random", "equal", "one long"])
+@pytest.mark.parametrize("own", [False, True])
+def test_ranked_and_balanced_heads(Hq, Hkv, M, B, counts, own):
+    """Per-head counts with one key range or more than one round of items (64 heads): heads
+    ranked by the pre-pass, or runs of heads where their counts are balanced."""
+    print(f"ranked Hq={Hq} Hkv={Hkv} M={M} counts={counts} own={own}", flush=True)
+    dh, N = 64, 200
+    rng = np.random.default_rng(Hq + M)
+    Q, K, V = normal(1, M, Hq, dh), normal(2, Hkv, N, dh), normal(3, Hkv, N, dh)
+    Ks, Vs = normal(4, Hkv, M, dh), normal(5, Hkv, M, dh)
+    idx = np.stack([rng.permutation(N)[:B] for _ in range(Hkv)]).astype(np.int32)
+    cnt = rng.integers(1, B + 1, size=Hkv).astype(np.int32)
+    if counts != "random":
+        cnt[:] = B if counts == "equal" else 1
+        cnt[Hkv // 2] = B
+    kw = dict(idx=torch.from_numpy(idx).to(DEV), counts=torch.from_numpy(cnt).to(DEV))
+    if own:
+        got = pkv.attend_chunk(Q, K, V, Ks, Vs, p_terms=2, **kw)
+    else:
+        got = pkv.attend_compressed(Q, K, V, **kw)
+    got = host(got).reshape(M, Hq, dh)
+    q, k, v, ks, vs = (host(t) for t in (Q, K, V, Ks, Vs))
+    for h in range(Hq):
+        g = h // (Hq // Hkv)
+        use = idx[g, :cnt[g]]
+        ref = attend(q[:, h], k[g, use], v[g, use], (ks[g], vs[g]) if own else None)
+        assert rel(got[:, h], ref) <= 5e-5, h
+
+
 def test_chunk_prefix_longer_than_the_cache():
     """A chunk whose own prefix is most of the work: whole own tiles below the diagonal run
     unmasked, the last ones masked; scores outgrowing the first tile at the diagonal."""
